@@ -8,9 +8,17 @@ namespace ssd {
 
 constexpr uint32_t MAX_ROWS = 16;
 constexpr uint32_t MAX_MERGE_SOURCES = 64;
-constexpr uint32_t SORT_SMALL = 8192;   // result lists up to this size sort in one block's LDS
+constexpr uint32_t SORT_SMALL = 8192;   // result lists up to this size are ranked by counting (k_sort_keep)
 constexpr uint32_t MAX_LINKS = 1024;    // detectors in one batch
 constexpr uint32_t LEVEL_VERIFY = 0xFFFFu;
+constexpr uint32_t LEVEL_DFS = 0xFFFEu;
+// The depth-first expansion's LDS: the links' prefix; per wave a queue of
+// DFS_QUEUE partial tuples a row and DFS_OUT full tuples; the hot columns of
+// rows 0 and 1 (up to DFS_LIST each); the packed hot bits of rows 2.. .  At q =
+// 16, r = 6: 64 + 16 + 16 + 32 KiB.  DFS_LDS_BYTES: 160 KiB less its static words.
+constexpr uint32_t DFS_QUEUE = 128, DFS_OUT = 256, DFS_LIST = 2048, DFS_LDS_BYTES = 156u * 1024u;
+__host__ __device__ inline uint32_t dfs_row_words(uint32_t q) { return q > 5u ? 1u << (q - 5u) : 1u; }
+inline uint64_t dfs_table_bytes(uint32_t q, uint32_t r) { return (uint64_t)(r - 2u) * dfs_row_words(q) * 4u; }
 
 // Device control block of one detector: counters written by the kernels.
 struct Ctl {
@@ -183,7 +191,8 @@ struct DetectArgs {
 struct LevelArgs {
     const LinkDesc* links;
     uint32_t n_links;
-    uint32_t level;               // 0 = rows 0..2, L = row L+2, LEVEL_VERIFY = final test
+    uint32_t level;               // 0 = rows 0..2, L = row L+2, LEVEL_DFS = every row, LEVEL_VERIFY = final test
+    uint32_t queue_rows;          // LEVEL_DFS: rows with a queue
 };
 
 struct MergeArgs {
@@ -244,7 +253,8 @@ hipError_t launch_hot_detect(const DetectArgs& a, uint32_t max_chunks_per_lane, 
 hipError_t launch_hot_detect16(const DetectArgs& a, hipStream_t s);
 hipError_t launch_hot_compact(const LinkDesc* links, const uint32_t* row_table, uint32_t rows, hipStream_t s);
 hipError_t launch_expand0(const LevelArgs& a, hipStream_t s);
-hipError_t launch_expand_dfs(const LevelArgs& a, uint32_t max_r, hipStream_t s);
+// the largest r, delta and dfs_table_bytes of the links
+hipError_t launch_expand_dfs(LevelArgs a, uint32_t max_r, uint32_t max_delta, uint64_t table_bytes, hipStream_t s);
 hipError_t launch_extend(const LevelArgs& a, hipStream_t s);
 hipError_t launch_verify(const LevelArgs& a, hipStream_t s);
 hipError_t launch_sort_small(const LinkDesc* links, uint32_t n_links, hipStream_t s);

@@ -1201,14 +1201,23 @@ __device__ __forceinline__ void count_body(const LinkDesc* D, uint64_t n_se, uin
         const bool hi = (e & 0x100u) != 0u, ei = (e & 0x200u) != 0u;
         uint4* se = reinterpret_cast<uint4*>(D->state + (si << log2eta));
         uint16_t* snap = D->live16 + si * chunks;
-        for (uint32_t c = lane; c < chunks; c += 64u) {
-            const uint4 v = se[c];
-            if (hi) snap[c] = (uint16_t)live_mask16(v, L);
-            if (ei) {
-                uint4 n;
-                n.x = expire_word(v.x, L); n.y = expire_word(v.y, L);
-                n.z = expire_word(v.z, L); n.w = expire_word(v.w, L);
-                if (n.x != v.x || n.y != v.y || n.z != v.z || n.w != v.w) se[c] = n;
+        // four chunks of a lane in flight (one after another: 26 against 22 us
+        // for the core link's 393K counters and 6500 hot estimators)
+        for (uint32_t c0 = lane; c0 < chunks; c0 += 256u) {
+            uint4 v[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; u++) v[u] = se[c0 + 64u * u < chunks ? c0 + 64u * u : c0];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; u++) {
+                const uint32_t c = c0 + 64u * u;
+                if (c >= chunks) continue;
+                if (hi) snap[c] = (uint16_t)live_mask16(v[u], L);
+                if (ei) {
+                    uint4 n;
+                    n.x = expire_word(v[u].x, L); n.y = expire_word(v[u].y, L);
+                    n.z = expire_word(v[u].z, L); n.w = expire_word(v[u].w, L);
+                    if (n.x != v[u].x || n.y != v[u].y || n.z != v[u].z || n.w != v[u].w) se[c] = n;
+                }
             }
         }
         if (hi) hot_finish<false>(D, si, todo_live[i], se, lane);
@@ -1314,19 +1323,30 @@ __global__ __launch_bounds__(1024) void k_hot_compact(const LinkDesc* links, con
 // Work items of one level for every link, prefix-summed; expansion levels pad
 // each link to whole 256-item blocks so that a block never spans two links.
 
+// log2 of the lanes that test one tuple: 128 cells of an estimator each (eta
+// >= 1024), at most a wave.
+__device__ __forceinline__ uint32_t verify_lanes_log2(uint32_t log2eta) { return min(6u, log2eta - 7u); }
+
 // Work items of one link at a level: 0 = |HSE(0)| x |HSE(1)| pairs of rows
-// 0, 1; L = the tuples of level L-1 (extended by row L+2); LEVEL_VERIFY = the
-// full tuples.  Expansion items are padded to whole 256-item workgroups, so a
-// workgroup never spans two links and appends with one atomic.
+// 0, 1; L = the tuples of level L-1 (extended by row L+2); LEVEL_DFS = waves'
+// worth of pairs of rows 0, 1 (extended over all rows); LEVEL_VERIFY = the
+// waves' worth of full tuples.  The items of levels 0 and L are padded to
+// whole 256-item workgroups, so a workgroup never spans two links and appends
+// with one atomic.
 __device__ __forceinline__ unsigned long long level_items(const LinkDesc* D, uint32_t level)
 {
     const Ctl* c = D->ctl;
     unsigned long long n = 0;
     if (level == 0) {
         n = (unsigned long long)c->hot_n[0] * c->hot_n[1];
+    } else if (level == LEVEL_DFS) {
+        // a wave takes 64 pairs
+        return ((unsigned long long)c->hot_n[0] * c->hot_n[1] + 63ull) >> 6;
     } else if (level == LEVEL_VERIFY) {
+        // a wave takes 64 / (lanes per tuple) tuples at a time
         const unsigned long long m = c->level_n[D->r - 3];
-        return m < D->max_tuples ? m : D->max_tuples;
+        const uint32_t sh = 6u - verify_lanes_log2(D->log2eta);
+        return ((m < D->max_tuples ? m : D->max_tuples) + (1ull << sh) - 1ull) >> sh;
     } else if (level + 2 < D->r) {
         const unsigned long long m = c->level_n[level - 1];
         n = m < D->max_tuples ? m : D->max_tuples;
@@ -1334,9 +1354,9 @@ __device__ __forceinline__ unsigned long long level_items(const LinkDesc* D, uin
     return (n + 255ull) & ~255ull;
 }
 
-// Every 256-thread workgroup of a level kernel computes the level's prefix of
-// work items over the links into LDS (pre[0..n_links]) from the counters the
-// previous kernel left: no separate launch between levels.
+// Every workgroup (of at least 256 threads) of a level kernel computes the
+// level's prefix of work items over the links into LDS (pre[0..n_links]) from
+// the counters the previous kernel left: no separate launch between levels.
 __device__ void level_prefix_lds(const LevelArgs& a, unsigned long long* pre)
 {
     __shared__ unsigned long long part[256];
@@ -1348,23 +1368,24 @@ __device__ void level_prefix_lds(const LevelArgs& a, unsigned long long* pre)
         __syncthreads();
         return;
     }
+    const bool in = threadIdx.x < 256u;
     const uint32_t per = (a.n_links + 255u) / 256u;
-    const uint32_t l0 = min(a.n_links, threadIdx.x * per), l1 = min(a.n_links, l0 + per);
+    const uint32_t l0 = in ? min(a.n_links, threadIdx.x * per) : a.n_links, l1 = min(a.n_links, l0 + per);
     unsigned long long sum = 0;
     for (uint32_t l = l0; l < l1; l++) {
         const unsigned long long n = level_items(a.links + l, a.level);
         pre[l] = n;
         sum += n;
     }
-    part[threadIdx.x] = sum;
+    if (in) part[threadIdx.x] = sum;
     __syncthreads();
     for (uint32_t o = 1; o < 256u; o <<= 1) {
-        const unsigned long long v = threadIdx.x >= o ? part[threadIdx.x - o] : 0ull;
+        const unsigned long long v = in && threadIdx.x >= o ? part[threadIdx.x - o] : 0ull;
         __syncthreads();
-        part[threadIdx.x] += v;
+        if (in) part[threadIdx.x] += v;
         __syncthreads();
     }
-    unsigned long long run = part[threadIdx.x] - sum;
+    unsigned long long run = in ? part[threadIdx.x] - sum : 0ull;
     for (uint32_t l = l0; l < l1; l++) {
         const unsigned long long n = pre[l];
         pre[l] = run;
@@ -1481,17 +1502,275 @@ __global__ __launch_bounds__(256) void k_extend(LevelArgs a)
 
 // ---------------------------------------------------------------- depth-first expansion
 // The same candidate tuples as the level-by-level kernels above, in one
-// launch: each thread takes one (HSE(0), HSE(1)) pair and extends it row by
-// row depth first; rows are template levels, so the loop state of every row
-// lives in registers.  A count pass reserves the workgroup's slots in the
-// full-tuple buffer, a second pass writes them.  Every level's tuple count
-// still goes to level_n (capacity checks and diagnostics).
+// launch.  Every level's tuple count still goes to level_n (capacity checks
+// and diagnostics); the order of the tuples is not deterministic.
+//
+// Few of the |HSE(0)| x |HSE(1)| pairs extend, and those unevenly, so a
+// thread per pair leaves most lanes of a wave idle, and nested loops over the
+// rows step through the product of its lanes' longest rows.  Here every wave
+// keeps a queue per row in LDS, of partial tuples with candidates of that row
+// left, and each of its steps works for up to 64 of them:
+//   - 64 pairs at a time, far apart in the list of pairs (a host's estimators
+//     extend in bulk, its neighbours not at all), are looked up; those with
+//     candidates of row 2 enter its queue;
+//   - a step takes the 64 newest partial tuples of the deepest row that has
+//     64, and of each its next candidate: the extended tuple enters the next
+//     row's queue (or, after the last row, the output), the tuple itself goes
+//     back while it has candidates left.  So no queue ever holds more than
+//     127, and the lanes are full until the end.
+// All lookups go to LDS: the hot bits of rows 2..r-1, 2^q per row in key order
+// (bit (key << delta) + j), and the hot columns of rows 0 and 1.  The walk
+// counts the tuples and keeps a wave's first DFS_OUT full ones in LDS; the
+// workgroup then reserves its slots with one atomic, and a wave with more
+// tuples walks again to write them (atomics of one address pass at about 12 ns
+// each: appending 192 tuples at a time took 84 us for 1.4M of them).  For
+// delta <= 6 (one 64-bit word of candidates a key) and links whose hot bits
+// leave room for the queues; others take the nested walk of k_expand_nested.
 
+// A wave's view of the link it expands.
+struct DfsLink {
+    const uint32_t* tab;              // packed hot bits of rows 2..
+    uint4* queue;                     // [r - 2][DFS_QUEUE]: x, he_0, candidates left
+    uint2* out;                       // [DFS_OUT]: the wave's first full tuples (x, he_0)
+    uint64_t* out_x;
+    uint32_t* out_h0;
+    uint64_t max_tuples;
+    uint32_t words, delta, sh, kmask, qmask, key_bits, r;
+};
+
+// Orders a wave's LDS accesses across its lanes.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// The candidates of `row` under a key, as a word of up to 2^6 bits.
+__device__ __forceinline__ uint64_t dfs_candidates(const DfsLink& d, uint32_t row, uint32_t key)
+{
+    const uint32_t bit = key << d.delta;
+    const uint32_t* w = d.tab + (row - 2u) * d.words + (bit >> 5);
+    if (d.delta == 6u) return (uint64_t)w[1] << 32 | w[0];
+    if (d.delta == 5u) return w[0];
+    return (w[0] >> (bit & 31u)) & ((1u << (1u << d.delta)) - 1u);
+}
+
+// The packed hot bits of rows 2..r-1 of link D (delta <= 6) into LDS.
+__device__ __forceinline__ void load_hot_table(const LinkDesc* D, uint32_t words, uint32_t* tab)
+{
+    const uint32_t delta = D->delta, sh = D->q - delta, n = (D->r - 2u) * words;
+    const uint32_t lg = 31u - (uint32_t)__clz((int)words);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(D->hotT);
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint32_t row = 2u + (i >> lg), w = i & (words - 1u);       // words per row: a power of two
+        uint32_t v = 0;
+        if (delta == 6u) {
+            v = src[(uint64_t)row * words + w];              // a 64-bit word a key: the same order
+        } else {
+            // one 64-bit word a key, its low 2^delta bits in use
+            const uint32_t key0 = (w << 5) >> delta, keys = min(32u >> delta, 1u << sh);
+            for (uint32_t m = 0; m < keys; m++)
+                v |= src[2u * (((uint64_t)row << sh) + key0 + m)] << (m << delta);
+        }
+        tab[i] = v;
+    }
+}
+
+// A wave's walk over its work items it, it + step, .. below `end` of n_items:
+// item i is the pairs i + lane * n_items of n0 x n1.  The tuples accepted per
+// level are added to lv (LDS, this wave's) and the first DFS_OUT full ones
+// staged; with `emit` the full ones go to slot, slot + 1, .. instead.  One loop, one copy of the step
+// whatever the row: a close runs this code once, so every cache line of it is
+// fetched cold (the step unrolled over the rows, in both walks, took 15 us
+// where there was next to nothing to expand).
+__device__ __forceinline__ void dfs_walk(const DfsLink& d, const uint32_t* l0, const uint32_t* l1, uint32_t n0,
+                                         uint32_t n1, uint64_t n_items, uint64_t it, uint64_t step, uint64_t end,
+                                         uint32_t* lv, bool emit, uint64_t slot)
+{
+    const uint64_t Q = (uint64_t)n0 * n1;
+    const uint32_t lane = threadIdx.x & 63u;
+    uint64_t cnt = 0;                   // the queues' sizes (at most 127), a byte each, from row 2's up
+    for (;;) {
+        // the newest entries of the deepest row that fills the wave; else new
+        // pairs; else the first row with any (what it adds fills the others)
+        const uint64_t full = cnt & 0x4040404040404040ull;
+        uint32_t level, x = 0, he0 = 0, next = 2;
+        uint64_t c = 0;                 // candidates of row `next` of the tuple (he0, x)
+        if (!full && it < end) {
+            const uint64_t p = it + lane * n_items;
+            it += step;
+            level = ~0u;
+            if (p < Q) {
+                const uint32_t ia = Q <= 0xFFFFFFFFull ? (uint32_t)p / n1 : (uint32_t)(p / n1);
+                he0 = l0[ia];
+                x = (he0 ^ l1[(uint32_t)(p - (uint64_t)ia * n1)]) & d.qmask;     // B(1): host bits 0..q-1
+                if (d.key_bits >= 32u || (x >> d.key_bits) == 0u) c = 1ull;
+            }
+        } else {
+            if (!cnt) break;
+            level = (full ? 63u - (uint32_t)__clzll((long long)full) : (uint32_t)__ffsll((long long)cnt) - 1u) >> 3;
+            const uint32_t row = level + 2u, n = (uint32_t)(cnt >> (8u * level)) & 0xFFu;
+            const uint32_t m = min(64u, n), base = n - m;
+            uint4* q = d.queue + level * DFS_QUEUE;
+            const bool in = lane < m;
+            uint4 t = make_uint4(0u, 0u, 0u, 0u);
+            if (in) t = q[base + lane];
+            wave_sync();
+            he0 = t.y;
+            uint64_t bits = (uint64_t)t.w << 32 | t.z;
+            const uint32_t j = (uint32_t)__ffsll((long long)bits) - 1u;
+            bits &= bits - 1ull;
+            // back while candidates are left
+            const uint64_t back = __ballot(in && bits != 0ull);
+            if (in && bits != 0ull) q[base + lanes_below(back)] = make_uint4(t.x, he0, (uint32_t)bits, (uint32_t)(bits >> 32));
+            cnt -= (uint64_t)(m - (uint32_t)__popcll(back)) << (8u * level);
+            // the top delta bits of B(row), host bits pos..; none may lie beyond the key width
+            const uint32_t pos = (row - 1u) * d.delta + d.sh;
+            const uint32_t v = ((he0 >> d.sh) ^ j) & ((1u << d.delta) - 1u);
+            const bool ok = in && (d.key_bits >= pos + d.delta || (v >> (d.key_bits > pos ? d.key_bits - pos : 0u)) == 0u);
+            x = pos < 32u ? t.x | (v << pos) : t.x;
+            const uint64_t good = __ballot(ok);
+            next = row + 1u;
+            c = ok ? 1ull : 0ull;
+            if (!emit && lane == 0) lv[level] += (uint32_t)__popcll(good);
+            if (next == d.r) {
+                const uint64_t at = slot + lanes_below(good);
+                if (ok && !emit && at < DFS_OUT) d.out[at] = make_uint2(x, he0);
+                if (ok && emit && at < d.max_tuples) {
+                    d.out_x[at] = x;
+                    d.out_h0[at] = he0;
+                }
+                slot += (uint64_t)__popcll(good);
+            }
+        }
+        if (next < d.r) {
+            if (c) c = dfs_candidates(d, next, ((((x >> ((next - 2u) * d.delta)) & d.qmask) >> d.delta) ^ he0) & d.kmask);
+            const uint64_t on = __ballot(c != 0ull);
+            const uint32_t sh = 8u * (next - 2u);
+            if (c) d.queue[(next - 2u) * DFS_QUEUE + ((uint32_t)(cnt >> sh) & 0xFFu) + lanes_below(on)] =
+                       make_uint4(x, he0, (uint32_t)c, (uint32_t)(c >> 32));
+            cnt += (uint64_t)__popcll(on) << sh;
+        }
+        wave_sync();
+    }
+}
+
+// One link's items are dealt to all waves in turn; several links' in
+// contiguous runs per workgroup, so that it meets few links and loads few
+// tables.
+template <int LEVELS, uint32_t WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
+{
+    // [n_links + 1] prefix; per wave the queues and the staged tuples; hot
+    // columns of rows 0 and 1; packed hot bits
+    extern __shared__ __align__(16) unsigned long long pre[];
+    __shared__ uint32_t lv_wave[WAVES][LEVELS];
+    __shared__ unsigned long long out_base;
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    const bool one = a.n_links == 1u;
+    if (!one) level_prefix_lds(a, pre);
+    uint4* queues = reinterpret_cast<uint4*>(pre + ((a.n_links + 2u) & ~1u));
+    uint2* outs = reinterpret_cast<uint2*>(queues + WAVES * a.queue_rows * DFS_QUEUE);
+    uint32_t* lists = reinterpret_cast<uint32_t*>(outs + WAVES * DFS_OUT);
+    uint32_t* tab = lists + 2u * DFS_LIST;
+    const uint64_t n_items = one ? level_items(a.links, LEVEL_DFS) : pre[a.n_links];
+    uint64_t item = one ? 0u : n_items * blockIdx.x / gridDim.x;
+    const uint64_t end = one ? n_items : n_items * (blockIdx.x + 1ull) / gridDim.x;
+    if (one && (uint64_t)blockIdx.x >= n_items) return;
+    while (item < end) {
+        // the run of this workgroup's items that belong to one link
+        const uint32_t l = one ? 0u : uniform(find_link(pre, a.n_links, item));
+        const LinkDesc* D = a.links + l;
+        const uint64_t link0 = one ? 0ull : pre[l], link_items = (one ? n_items : pre[l + 1]) - link0;
+        const uint64_t run_end = min(link0 + link_items, end);
+        const uint32_t n0 = D->ctl->hot_n[0], n1 = D->ctl->hot_n[1], lf = D->r - 3u;
+        DfsLink d;
+        d.delta = D->delta; d.sh = D->q - d.delta; d.r = D->r; d.key_bits = D->key_bits;
+        d.kmask = (1u << d.sh) - 1u;
+        d.qmask = (1u << D->q) - 1u;
+        d.words = dfs_row_words(D->q);
+        d.max_tuples = D->max_tuples;
+        d.out_x = D->ctb_x[lf & 1u];
+        d.out_h0 = D->ctb_h0[lf & 1u];
+        d.tab = tab;
+        d.queue = queues + wid * a.queue_rows * DFS_QUEUE;
+        d.out = outs + wid * DFS_OUT;
+        const uint32_t *l0 = D->hot_list, *l1 = D->hot_list + (1ull << D->q);
+        if (lane < (uint32_t)LEVELS) lv_wave[wid][lane] = 0u;
+        if (n0 <= DFS_LIST && n1 <= DFS_LIST) {          // (longer lists are read where they are)
+            const uint32_t n = max(n0, n1);
+            for (uint32_t i = threadIdx.x; i < n; i += 64u * WAVES) {
+                const uint32_t c0 = l0[min(i, n0 - 1u)], c1 = l1[min(i, n1 - 1u)];
+                lists[i] = c0;
+                lists[DFS_LIST + i] = c1;
+            }
+            l0 = lists;
+            l1 = lists + DFS_LIST;
+        }
+        load_hot_table(D, d.words, tab);
+        __syncthreads();
+        const uint64_t it = one ? (uint64_t)wid * gridDim.x + blockIdx.x : item - link0 + wid;
+        const uint64_t step = one ? (uint64_t)gridDim.x * WAVES : WAVES, it_end = run_end - link0;
+        uint64_t slot = 0;
+        for (uint32_t pass = 0; pass < 2u; pass++) {
+            const uint32_t mine = lv_wave[wid][lf];          // the wave's full tuples, once counted
+            if (pass && mine <= DFS_OUT) {
+                for (uint32_t i = lane; i < mine; i += 64u) {
+                    const uint2 v = d.out[i];
+                    if (slot + i < d.max_tuples) {
+                        d.out_x[slot + i] = v.x;
+                        d.out_h0[slot + i] = v.y;
+                    }
+                }
+            } else {
+                dfs_walk(d, l0, l1, n0, n1, link_items, it, step, it_end, lv_wave[wid], pass != 0u, slot);
+            }
+            __syncthreads();
+            if (pass) break;
+            if (threadIdx.x <= lf) {
+                unsigned long long v = 0;
+                for (uint32_t w = 0; w < WAVES; w++) v += lv_wave[w][threadIdx.x];
+                const unsigned long long at = v ? atomicAdd(&D->ctl->level_n[threadIdx.x], v) : 0ull;
+                if (threadIdx.x == lf) out_base = at;
+            }
+            __syncthreads();
+            slot = out_base;
+            for (uint32_t w = 0; w < wid; w++) slot += lv_wave[w][lf];
+        }
+        item = run_end;
+    }
+}
+
+// Level-0 pair idx of n0 x n1: (he0, B(1)); false if idx is padding or B(1)
+// has bits beyond the key width.
+__device__ __forceinline__ bool level0_pair(const LinkDesc* D, uint64_t idx, uint32_t* he0, uint64_t* x)
+{
+    const uint64_t n0 = D->ctl->hot_n[0], n1 = D->ctl->hot_n[1];
+    const uint64_t Q = n0 * n1;
+    if (idx >= Q) return false;
+    uint64_t ia, ib;
+    if (Q <= 0xFFFFFFFFull) { ia = (uint32_t)idx / (uint32_t)n1; ib = (uint32_t)idx - (uint32_t)ia * (uint32_t)n1; }
+    else { ia = idx / n1; ib = idx % n1; }
+    *he0 = D->hot_list[ia];
+    const uint32_t he1 = D->hot_list[(1ull << D->q) + ib];
+    *x = (uint64_t)((*he0 ^ he1) & ((1u << D->q) - 1u));                 // B(1): host bits 0..q-1
+    return (*x >> D->key_bits) == 0;
+}
+
+// The nested walk, with the hot bits in memory: rows are template levels, so
+// the loop state of every row lives in registers; each thread takes pairs of
+// HSE(0) x HSE(1).  A count pass reserves the workgroup's slots in the
+// full-tuple buffer, a second pass writes them.
 template <int RMAX>
 struct DfsCtx {
     uint32_t lv[RMAX];            // tuples accepted per level, this thread
-    uint32_t full;                // full tuples, this thread
-    uint64_t slot;                // write pass: first slot of this thread
+    uint64_t slot;                // write pass: this thread's next slot
     uint64_t* out_x;
     uint32_t* out_h0;
 };
@@ -1503,13 +1782,12 @@ __device__ __forceinline__ void dfs_row(const LinkDesc* D, uint32_t he0, uint64_
 {
     if (ROW == RMAX || (uint32_t)ROW >= D->r) {             // rows 0..r-1 all chosen: a full tuple
         if (EMIT) {
-            const uint64_t i = c.slot + c.full;
-            if (i < D->max_tuples) {
-                c.out_x[i] = x;
-                c.out_h0[i] = he0;
+            if (c.slot < D->max_tuples) {
+                c.out_x[c.slot] = x;
+                c.out_h0[c.slot] = he0;
             }
+            c.slot++;
         }
-        c.full++;
         return;
     }
     if constexpr (ROW < RMAX) {
@@ -1535,88 +1813,71 @@ __device__ __forceinline__ void dfs_row(const LinkDesc* D, uint32_t he0, uint64_
     }
 }
 
-// Level-0 pair idx of link D: (he0, B(1)); false if idx is padding or B(1)
-// has bits beyond the key width.
-__device__ __forceinline__ bool level0_pair(const LinkDesc* D, uint64_t idx, uint32_t* he0, uint64_t* x)
+// A workgroup's slots for its threads' tuples of one link: the totals per
+// level to level_n, and this thread's first full-tuple slot (base of the
+// workgroup, then the tuples of the lanes and waves before it).  lv: tuples
+// per level (the last one are the full ones).  All threads call it.
+template <int RMAX>
+__device__ __forceinline__ uint64_t reserve_tuples(const LinkDesc* D, const uint32_t* lv, uint32_t (*wsum)[RMAX],
+                                                   unsigned long long* base_slot)
 {
-    const uint64_t n0 = D->ctl->hot_n[0], n1 = D->ctl->hot_n[1];
-    const uint64_t Q = n0 * n1;
-    if (idx >= Q) return false;
-    uint64_t ia, ib;
-    if (Q <= 0xFFFFFFFFull) { ia = (uint32_t)idx / (uint32_t)n1; ib = (uint32_t)idx - (uint32_t)ia * (uint32_t)n1; }
-    else { ia = idx / n1; ib = idx % n1; }
-    *he0 = D->hot_list[ia];
-    const uint32_t he1 = D->hot_list[(1ull << D->q) + ib];
-    *x = (uint64_t)((*he0 ^ he1) & ((1u << D->q) - 1u));                 // B(1): host bits 0..q-1
-    return (*x >> D->key_bits) == 0;
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    const uint32_t r = D->r, lf = r - 3;
+    uint32_t full = 0;
+#pragma unroll
+    for (uint32_t L = 0; L + 2 < (uint32_t)RMAX; L++) {
+        if (L == lf) full = lv[L];
+        const uint32_t v = wave_sum(L <= lf ? lv[L] : 0u);
+        if (lane == 0) wsum[wid][L] = v;
+    }
+    uint32_t incl = full;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(incl, o, 64);
+        if (lane >= (uint32_t)o) incl += v;
+    }
+    __syncthreads();
+    if (threadIdx.x <= lf) {
+        const uint32_t L = threadIdx.x;
+        unsigned long long v = 0;
+        for (uint32_t w = 0; w < 4u; w++) v += wsum[w][L];
+        const unsigned long long at = v ? atomicAdd(&D->ctl->level_n[L], v) : 0ull;
+        if (L == lf) *base_slot = at;
+    }
+    __syncthreads();
+    uint64_t before = 0;
+    for (uint32_t w = 0; w < wid; w++) before += wsum[w][lf];
+    return *base_slot + before + (incl - full);
 }
 
-// Grid-stride over every link's level-0 pairs.  Pass 1 counts (per level and
-// full tuples) in registers; the workgroup then reserves its slots for each
-// link once, with one atomic per link and level; pass 2 repeats the walk and
-// writes.  A workgroup's 256-item chunks never span two links (padding), and
-// a workgroup handles chunks of one link at a time, so per-link totals are
-// flushed whenever the link changes.
 template <int RMAX>
-__global__ __launch_bounds__(256) void k_expand_dfs(LevelArgs a)
+__global__ __launch_bounds__(256) void k_expand_nested(LevelArgs a)
 {
     extern __shared__ unsigned long long pre[];      // [n_links + 1], sized at launch
     __shared__ uint32_t wsum[4][RMAX];
     __shared__ unsigned long long base_slot;
     level_prefix_lds(a, pre);
-    const uint64_t total = pre[a.n_links];
-    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    const uint64_t n_chunks = pre[a.n_links] / 256u;
     uint64_t chunk = blockIdx.x;
-    const uint64_t n_chunks = total / 256u;
     while (chunk < n_chunks) {
         // the run of this workgroup's chunks that belong to one link
         const uint32_t l = uniform(find_link(pre, a.n_links, chunk * 256u));
         const LinkDesc* D = a.links + l;
         const uint64_t link_end = pre[l + 1] / 256u;
-        const uint32_t lf = D->r - 3;
         DfsCtx<RMAX> c{};
-        c.out_x = D->ctb_x[lf & 1];
-        c.out_h0 = D->ctb_h0[lf & 1];
+        c.out_x = D->ctb_x[(D->r - 3u) & 1u];
+        c.out_h0 = D->ctb_h0[(D->r - 3u) & 1u];
         uint64_t ch = chunk;
         for (; ch < link_end; ch += gridDim.x) {
             uint32_t he0;
             uint64_t x;
             if (level0_pair(D, ch * 256u - pre[l] + threadIdx.x, &he0, &x)) dfs_row<2, RMAX, false>(D, he0, x, c);
         }
-        // workgroup totals per level; the last level is the full tuples
-#pragma unroll
-        for (uint32_t L = 0; L < (uint32_t)RMAX; L++) {
-            const uint32_t v = wave_sum(L + 3 <= D->r ? (L + 3 == D->r ? c.full : c.lv[L]) : 0u);
-            if (lane == 0) wsum[wid][L] = v;
-        }
-        __syncthreads();
-        if (threadIdx.x < (uint32_t)RMAX && threadIdx.x + 3 <= D->r) {
-            const uint32_t L = threadIdx.x;
-            const unsigned long long v = (unsigned long long)wsum[0][L] + wsum[1][L] + wsum[2][L] + wsum[3][L];
-            if (L + 3 == D->r) base_slot = v ? atomicAdd(&D->ctl->level_n[L], v) : 0ull;
-            else if (v) atomicAdd(&D->ctl->level_n[L], v);
-        }
-        // this thread's first slot: the workgroup's base plus the full
-        // tuples of the lanes and waves before it
-        uint32_t incl = c.full;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(incl, o, 64);
-            if (lane >= (uint32_t)o) incl += v;
-        }
-        __syncthreads();
-        uint64_t before = 0;
-        for (uint32_t w = 0; w < wid; w++) before += wsum[w][lf];
-        if (c.full) {
-            DfsCtx<RMAX> e{};
-            e.out_x = c.out_x;
-            e.out_h0 = c.out_h0;
-            e.slot = base_slot + before + (incl - c.full);
-            for (uint64_t cw = chunk; cw < link_end; cw += gridDim.x) {
-                uint32_t he0;
-                uint64_t x;
-                if (level0_pair(D, cw * 256u - pre[l] + threadIdx.x, &he0, &x)) dfs_row<2, RMAX, true>(D, he0, x, e);
-            }
+        c.slot = reserve_tuples<RMAX>(D, c.lv, wsum, &base_slot);
+        for (uint64_t cw = chunk; cw < link_end; cw += gridDim.x) {
+            uint32_t he0;
+            uint64_t x;
+            if (level0_pair(D, cw * 256u - pre[l] + threadIdx.x, &he0, &x)) dfs_row<2, RMAX, true>(D, he0, x, c);
         }
         __syncthreads();
         chunk = ch;
@@ -1626,43 +1887,125 @@ __global__ __launch_bounds__(256) void k_expand_dfs(LevelArgs a)
 // ---------------------------------------------------------------- verify
 // Final test of every full tuple (end of Alg. 4, Sec. 4.2 last pass): optional
 // re-hash check, then the UnionSE of Alg. 1 -- a cell counts only when it is
-// live in all r estimators -- and R >= T.  One wave per tuple.
+// live in all r estimators -- and R >= T.
+//
+// Bound by the L2 reads of the live-cell snapshots.  eta / 128 lanes take a
+// tuple (one 16-byte load per row), so a wave tests 64 / lanes consecutive
+// tuples at a time: at eta = 2048 four, where a wave per tuple left half its
+// lanes idle and made 32 8-byte loads per row.  A union's count only falls
+// with every row, so the first three rows are counted first and the others
+// are read only for tuples that can still reach T: most false tuples cannot.
 
-__global__ __launch_bounds__(256) void k_verify(LevelArgs a)
+//
+// One link's accepted keys are collected in LDS and appended once per
+// workgroup: atomics of one address pass at about 12 ns each, 12 us for the
+// 1000 hosts of a small close (several links append to a counter each).
+// Measured against a wave and five full rows per tuple: 1.4M tuples at eta =
+// 2048, r = 5 508 -> 131 us (13.7 TB/s of snapshots); 6000 tuples with 1000
+// accepted at eta = 1024, r = 6 17 -> 10 us.
+
+constexpr uint32_t VERIFY_THREADS = 1024, VERIFY_LIST = 1024;
+
+__global__ __launch_bounds__(VERIFY_THREADS) void k_verify(LevelArgs a)
 {
     extern __shared__ unsigned long long pre[];      // [n_links + 1], sized at launch
+    __shared__ unsigned long long list[VERIFY_LIST], list_at;
+    __shared__ uint32_t n_list;
+    if (threadIdx.x == 0) n_list = 0u;
     level_prefix_lds(a, pre);
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t waves = (uint64_t)gridDim.x * 4u;
+    const uint64_t waves = (uint64_t)gridDim.x * (VERIFY_THREADS / 64u);
     const uint64_t total = pre[a.n_links];
-    for (uint64_t t = (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6); t < total; t += waves) {
-        const uint32_t l = uniform(find_link(pre, a.n_links, t));
-        const LinkDesc* D = a.links + l;
-        const uint64_t idx = t - pre[l];
-        const uint32_t lf = D->r - 3;
-        const uint32_t he0 = D->ctb_h0[lf & 1][idx];
-        const uint64_t x = D->ctb_x[lf & 1][idx];
-        const uint32_t q = D->q, qmask = (1u << q) - 1u;
-        if (D->rehash && (tab_hash(D->tables, (uint32_t)x) & qmask) != he0) continue;
-        // UnionSE (Alg. 1): a cell counts when it is live in all r estimators,
-        // from the live-cell snapshots hot detection took of these (hot) estimators
-        const uint32_t words = D->eta >> 6;                  // 64 cells per word
-        const uint64_t* snap = reinterpret_cast<const uint64_t*>(D->live16);
-        uint32_t cnt = 0;
-        for (uint32_t w = lane; w < words; w += 64u) {
-            uint64_t m = ~0ull;
-            for (uint32_t i = 0; i < D->r; i++) {
-                const uint32_t col = i == 0 ? he0 : (((uint32_t)(x >> ((i - 1) * D->delta)) & qmask) ^ he0);
-                m &= snap[((((uint64_t)i << q) | col) * words) + w];
-            }
-            cnt += __popcll(m);
+    // the link at hand, and the next tuple of these lanes: read while the one
+    // before it is tested
+    uint32_t l = ~0u, lg = 0, lanes = 0, r = 0, delta = 0, q = 0, qmask = 0, words = 0, T = 0;
+    bool rehash = false;
+    uint64_t n = 0, next_x = 0;
+    uint32_t next_he0 = 0;
+    bool next_ok = false;
+    const LinkDesc* D = nullptr;
+    const uint4* snap = nullptr;
+    const uint64_t* in_x = nullptr;
+    const uint32_t* in_h0 = nullptr;
+    auto fetch = [&](uint64_t t) {
+        const uint64_t idx = ((t - pre[l]) << (6u - lg)) + (lane >> lg);
+        next_ok = idx < n;
+        next_he0 = next_ok ? in_h0[idx] : 0u;
+        next_x = next_ok ? in_x[idx] : 0ull;
+    };
+    for (uint64_t t = (uint64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x; t < total; t += waves) {
+        if (l == ~0u || t >= pre[l + 1]) {
+            l = uniform(find_link(pre, a.n_links, t));
+            D = a.links + l;
+            lg = verify_lanes_log2(D->log2eta);
+            lanes = 1u << lg;
+            r = D->r; delta = D->delta; q = D->q; T = D->T;
+            qmask = (1u << q) - 1u;
+            words = D->eta >> 7;                             // 128 cells per load
+            rehash = D->rehash != 0u;
+            const unsigned long long raw = D->ctl->level_n[r - 3u];
+            n = raw < D->max_tuples ? raw : D->max_tuples;
+            // from the snapshots hot detection took of the (hot) estimators
+            snap = reinterpret_cast<const uint4*>(D->live16);
+            in_x = D->ctb_x[(r - 3u) & 1u];
+            in_h0 = D->ctb_h0[(r - 3u) & 1u];
+            fetch(t);
         }
-        const uint32_t R = wave_sum(cnt);
-        if (lane == 0 && R >= D->T) {
-            const unsigned long long i = atomicAdd(&D->ctl->n_acc, 1ull);
-            if (i < D->max_results) D->acc[i] = (x << 32) | (uint64_t)(0xFFFFFFFFu - R);
+        const uint32_t he0 = next_he0, sub = lane & (lanes - 1u);     // sub: this lane's place among its tuple's lanes
+        const uint64_t x = next_x;
+        bool ok = next_ok;
+        if (t + waves < pre[l + 1]) fetch(t + waves);
+        if (rehash && ok) ok = (tab_hash(D->tables, (uint32_t)x) & qmask) == he0;
+        if (!__any(ok)) continue;
+        auto row_words = [&](uint32_t i) {
+            const uint32_t col = i == 0 ? he0 : (((uint32_t)(x >> ((i - 1) * delta)) & qmask) ^ he0);
+            return snap + (((uint64_t)i << q) | col) * words;
+        };
+        // the union of rows i0 .. i1 (three at most, loaded together) with m
+        auto rows_and = [&](uint4& m, uint32_t w, uint32_t i0, uint32_t i1) {
+            const uint4 v0 = row_words(i0)[w], v1 = row_words(min(i0 + 1u, i1))[w], v2 = row_words(i1)[w];
+            m.x &= v0.x & v1.x & v2.x; m.y &= v0.y & v1.y & v2.y;
+            m.z &= v0.z & v1.z & v2.z; m.w &= v0.w & v1.w & v2.w;
+        };
+        // the count over all of a tuple's lanes
+        auto count = [&](const uint4& m) { return (uint32_t)(__popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w)); };
+        auto lanes_sum = [&](uint32_t v) {
+            for (uint32_t o = lanes >> 1; o > 0; o >>= 1) v += __shfl_xor(v, (int)o, 64);
+            return v;
+        };
+        uint32_t R = 0;
+        for (uint32_t w0 = 0; w0 < words; w0 += lanes) {
+            uint4 m = ok ? make_uint4(~0u, ~0u, ~0u, ~0u) : make_uint4(0u, 0u, 0u, 0u);
+            for (uint32_t i = 0; i < r; i += 3u) {
+                if (ok) rows_and(m, w0 + sub, i, min(i + 2u, r - 1u));
+                // an estimator in one load per row: tuples that cannot reach T any more end here
+                if (words <= 64u && i + 3u < r) {
+                    ok = ok && lanes_sum(count(m)) >= T;
+                    if (!__any(ok)) break;
+                }
+            }
+            R += count(m);
+        }
+        R = lanes_sum(R);
+        if (ok && sub == 0 && R >= T) {
+            const unsigned long long key = (x << 32) | (uint64_t)(0xFFFFFFFFu - R);
+            const uint32_t at = a.n_links == 1u ? atomicAdd(&n_list, 1u) : VERIFY_LIST;
+            if (at < VERIFY_LIST) {
+                list[at] = key;
+            } else {
+                const unsigned long long i = atomicAdd(&D->ctl->n_acc, 1ull);
+                if (i < D->max_results) D->acc[i] = key;
+            }
         }
     }
+    if (a.n_links != 1u) return;
+    __syncthreads();
+    const uint32_t found = min(n_list, VERIFY_LIST);
+    if (found == 0) return;
+    if (threadIdx.x == 0) list_at = atomicAdd(&a.links->ctl->n_acc, (unsigned long long)found);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < found; i += VERIFY_THREADS)
+        if (list_at + i < a.links->max_results) a.links->acc[list_at + i] = list[i];
 }
 
 // ---------------------------------------------------------------- sort + report
@@ -1695,56 +2038,119 @@ __device__ __forceinline__ void ctl_to_host(const LinkDesc* D, unsigned long lon
     }
 }
 
-// One block per link: up to SORT_SMALL keys sorted in LDS (bitonic),
-// de-duplicated by ip and written as the result list.  Lists above the link's
-// limit are left to the multi-kernel sort.
-__global__ __launch_bounds__(1024) void k_sort_small(const LinkDesc* links)
+// The list of up to sort_limit (<= SORT_SMALL) keys in two launches, ranked by
+// counting: every key's ip is compared with every other, 64 keys of a
+// workgroup in its lanes, the others split over its 16 waves and read from
+// LDS.  n^2 comparisons spread over the chip are far cheaper than one
+// workgroup's sort, a chain of log2(n)^2 / 2 barriers on one compute unit.
+//   k_sort_keep: a key stays if no other of its ip comes before it (larger R,
+//   or equal and earlier in the list); n_out counts them.  A kept key's ip
+//   goes to the link's idle candidate buffers (which hold at least as many
+//   tuples as passed; the flags to their he_0 half), the others become 2^32 -
+//   1 there, above or equal to every ip.
+//   k_sort_place: the place of a kept key is the number of kept ips below its.
+// Grid: links x workgroups, each taking 64 keys in turn.  Lists above the
+// link's limit are left to the multi-kernel sort.
+
+// The number of keys of this link's list that the small sort takes (0: none).
+__device__ __forceinline__ uint32_t rank_keys(const LinkDesc* D)
 {
-    __shared__ unsigned long long s[SORT_SMALL];
-    __shared__ uint32_t lds[16];
+    const uint64_t n = D->ctl->n_acc;
+    return n > D->sort_limit || n > D->max_results ? 0u : (uint32_t)n;
+}
+
+// Idle once the tuples are tested: the kept ips, and a flag per key.
+__device__ __forceinline__ uint32_t* rank_ips(const LinkDesc* D)
+{
+    return reinterpret_cast<uint32_t*>(D->ctb_x[((D->r - 3u) & 1u) ^ 1u]);
+}
+__device__ __forceinline__ uint32_t* rank_flags(const LinkDesc* D) { return D->ctb_h0[((D->r - 3u) & 1u) ^ 1u]; }
+
+// This wave's share of n values, four at a time (a multiple of 4 padded with
+// 2^32 - 1 is in `ips`): f(value, index).
+template <class F>
+__device__ __forceinline__ void for_ips(const uint32_t* ips, uint32_t n, F f)
+{
+    const uint32_t quads = (n + 3u) >> 2, per = (quads + 15u) >> 4, wave = threadIdx.x >> 6;
+    const uint32_t q1 = min(quads, (wave + 1u) * per);
+    for (uint32_t j = wave * per; j < q1; j++) {
+        const uint4 v = reinterpret_cast<const uint4*>(ips)[j];
+        f(v.x, 4u * j);
+        f(v.y, 4u * j + 1u);
+        f(v.z, 4u * j + 2u);
+        f(v.w, 4u * j + 3u);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_sort_keep(const LinkDesc* links)
+{
+    __shared__ __align__(16) uint32_t ips[SORT_SMALL];
+    __shared__ uint32_t before[64];
     const LinkDesc* D = links + blockIdx.x;
-    if (threadIdx.x == 0) D->clock->t += 1ull;       // the close's last kernel per link: the next slot opens
-    const uint64_t nraw = D->ctl->n_acc;
-    if (nraw > D->sort_limit || nraw > D->max_results) {
-        ctl_to_host(D, D->ctl->n_out);               // the host finishes this list
-        return;
-    }
-    const uint32_t n = (uint32_t)(nraw < SORT_SMALL ? nraw : SORT_SMALL);
+    const uint32_t n = rank_keys(D), lane = threadIdx.x & 63u;
+    if (blockIdx.y * 64u >= n) return;
     const unsigned long long* keys = D->acc;
-    uint32_t N = 1;
-    while (N < n) N <<= 1;
-    for (uint32_t i = threadIdx.x; i < N; i += 1024u) s[i] = i < n ? keys[i] : ~0ull;
-    __syncthreads();
-    for (uint32_t k = 2; k <= N; k <<= 1) {
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t i = threadIdx.x; i < N; i += 1024u) {
-                const uint32_t p = i ^ j;
-                if (p > i) {
-                    const unsigned long long u = s[i], v = s[p];
-                    const bool up = (i & k) == 0;
-                    if ((u > v) == up) { s[i] = v; s[p] = u; }
-                }
+    uint32_t *kept = rank_ips(D), *flags = rank_flags(D);
+    for (uint32_t i = threadIdx.x; i < ((n + 3u) & ~3u); i += 1024u) ips[i] = i < n ? (uint32_t)(keys[i] >> 32) : ~0u;
+    for (uint32_t i0 = blockIdx.y * 64u; i0 < n; i0 += gridDim.y * 64u) {
+        const uint32_t i = i0 + lane;
+        const unsigned long long k = i < n ? keys[i] : 0ull;
+        const uint32_t ip = (uint32_t)(k >> 32);
+        if (threadIdx.x < 64u) before[lane] = 0u;
+        __syncthreads();
+        for_ips(ips, n, [&](uint32_t o, uint32_t j) {
+            if (o == ip && j != i && j < n) {          // rare: another tuple regained this ip
+                const unsigned long long ko = keys[j];
+                if (ko < k || (ko == k && j < i)) before[lane] = 1u;
             }
-            __syncthreads();
+        });
+        __syncthreads();
+        if (threadIdx.x < 64u) {
+            const bool stays = i < n && !before[lane];
+            if (i < n) {
+                kept[i] = stays ? ip : ~0u;
+                flags[i] = stays ? 1u : 0u;
+            }
+            const uint64_t m = __ballot(stays);
+            if (lane == 0) atomicAdd(&D->ctl->n_out, (unsigned long long)__popcll(m));
         }
+        __syncthreads();
     }
-    const uint32_t per = (N + 1023u) / 1024u;
-    const uint32_t i0 = min(n, threadIdx.x * per), i1 = min(n, i0 + per);
-    uint32_t cnt = 0;
-    for (uint32_t i = i0; i < i1; i++) cnt += (i == 0 || (s[i] >> 32) != (s[i - 1] >> 32));
-    uint32_t total;
-    uint32_t off = block_exclusive_scan_1024(cnt, lds, &total);
-    for (uint32_t i = i0; i < i1; i++) {
-        if (i == 0 || (s[i] >> 32) != (s[i - 1] >> 32)) {
-            const uint32_t R = 0xFFFFFFFFu - (uint32_t)s[i];
+}
+
+__global__ __launch_bounds__(1024) void k_sort_place(const LinkDesc* links)
+{
+    __shared__ __align__(16) uint32_t ips[SORT_SMALL];
+    __shared__ uint32_t below[64];
+    const LinkDesc* D = links + blockIdx.x;
+    const uint32_t n = rank_keys(D), lane = threadIdx.x & 63u;
+    const uint32_t *kept = rank_ips(D), *flags = rank_flags(D);
+    if (blockIdx.y * 64u < n)
+        for (uint32_t i = threadIdx.x; i < ((n + 3u) & ~3u); i += 1024u) ips[i] = i < n ? kept[i] : ~0u;
+    for (uint32_t i0 = blockIdx.y * 64u; i0 < n; i0 += gridDim.y * 64u) {
+        const uint32_t i = i0 + lane;
+        const bool stays = i < n && flags[i];
+        if (threadIdx.x < 64u) below[lane] = 0u;
+        __syncthreads();
+        const uint32_t ip = i < n ? ips[i] : 0u;
+        uint32_t c = 0;
+        for_ips(ips, n, [&](uint32_t o, uint32_t) { c += o < ip ? 1u : 0u; });
+        if (c) atomicAdd(&below[lane], c);
+        __syncthreads();
+        if (threadIdx.x < 64u && stays) {
+            const uint32_t at = below[lane], R = 0xFFFFFFFFu - (uint32_t)D->acc[i];
             SuperPointDev sp;
-            sp.ip = (uint32_t)(s[i] >> 32); sp.rk = R; sp.est = estimate(D->eta, R);
-            if (off < D->host_cap) D->host_out[off] = sp;     // straight into the host's pinned mailbox
-            D->out[off++] = sp;
+            sp.ip = ip; sp.rk = R; sp.est = estimate(D->eta, R);
+            if (at < D->host_cap) D->host_out[at] = sp;       // straight into the host's pinned mailbox
+            D->out[at] = sp;
         }
+        __syncthreads();
     }
-    if (threadIdx.x == 0) D->ctl->n_out = total;
-    ctl_to_host(D, total);
+    if (blockIdx.y != 0) return;
+    // the link's first workgroup ends its close: the next slot opens (a list
+    // left to the multi-kernel sort is finished by the host)
+    ctl_to_host(D, D->ctl->n_out);
+    if (threadIdx.x == 0) D->clock->t += 1ull;
 }
 
 // Global bitonic step over N (power of two) keys, for lists above SORT_SMALL.
@@ -2138,19 +2544,43 @@ hipError_t launch_expand0(const LevelArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// workgroups of the depth-first expansion: each flushes its counts with one
-// atomic per level, so fewer is better until the grid stops filling the chip
-// (512 and 1024 measured equal, 2048 slower)
-// Grids of the close's small kernels (fewer workgroups, which would leave
-// more of the chip to the overlapping scan, made them slower than the scan:
-// 128/256 and 256/512 workgroups measured worse than 512/2048)
-constexpr uint32_t DFS_BLOCKS = 512;
-constexpr uint32_t VERIFY_BLOCKS = 2048;
-hipError_t launch_expand_dfs(const LevelArgs& a, uint32_t max_r, hipStream_t s)
+// workgroups of the depth-first expansion: one per compute unit (its LDS); of
+// the nested walk: each flushes its counts with one atomic per level, so
+// fewer is better until the grid stops filling the chip
+constexpr uint32_t DFS_BLOCKS = 256, NESTED_BLOCKS = 512;
+constexpr uint32_t VERIFY_BLOCKS = 512;         // two workgroups of 16 waves per compute unit
+
+// dynamic LDS of k_expand_dfs
+static uint64_t dfs_lds_bytes(uint32_t n_links, uint32_t rows, uint32_t waves, uint64_t table_bytes)
 {
-    if (max_r <= 6) k_expand_dfs<6><<<DFS_BLOCKS, 256, prefix_lds(a), s>>>(a);
-    else if (max_r <= 8) k_expand_dfs<8><<<DFS_BLOCKS, 256, prefix_lds(a), s>>>(a);
-    else return hipErrorInvalidValue;
+    return ((n_links + 2u) & ~1u) * 8ull + (uint64_t)waves * (rows * DFS_QUEUE * 16u + DFS_OUT * 8u) +
+           2ull * DFS_LIST * 4u + table_bytes;
+}
+
+hipError_t launch_expand_dfs(LevelArgs a, uint32_t max_r, uint32_t max_delta, uint64_t table_bytes, hipStream_t s)
+{
+    if (max_r < 3 || max_r > 8) return hipErrorInvalidValue;
+    // eight waves' queues at r <= 6, four at r <= 8 (48 KiB both at the most rows)
+    const uint32_t waves = max_r <= 6 ? 8u : 4u;
+    const uint64_t lds = dfs_lds_bytes(a.n_links, max_r - 2u, waves, table_bytes);
+    if (lds > DFS_LDS_BYTES || max_delta > 6) {
+        a.level = 0;
+        if (max_r <= 6) k_expand_nested<6><<<NESTED_BLOCKS, 256, prefix_lds(a), s>>>(a);
+        else k_expand_nested<8><<<NESTED_BLOCKS, 256, prefix_lds(a), s>>>(a);
+        return hipGetLastError();
+    }
+    a.level = LEVEL_DFS;
+    a.queue_rows = max_r - 2u;
+    static bool attr = false;
+    if (!attr) {
+        for (const void* f : {reinterpret_cast<const void*>(&k_expand_dfs<4, 8>), reinterpret_cast<const void*>(&k_expand_dfs<6, 4>)}) {
+            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DFS_LDS_BYTES);
+            if (e != hipSuccess) return e;
+        }
+        attr = true;
+    }
+    if (max_r <= 6) k_expand_dfs<4, 8><<<DFS_BLOCKS, 512, (uint32_t)lds, s>>>(a);
+    else k_expand_dfs<6, 4><<<DFS_BLOCKS, 256, (uint32_t)lds, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2162,13 +2592,16 @@ hipError_t launch_extend(const LevelArgs& a, hipStream_t s)
 
 hipError_t launch_verify(const LevelArgs& a, hipStream_t s)
 {
-    k_verify<<<VERIFY_BLOCKS, 256, prefix_lds(a), s>>>(a);
+    k_verify<<<VERIFY_BLOCKS, VERIFY_THREADS, prefix_lds(a), s>>>(a);
     return hipGetLastError();
 }
 
 hipError_t launch_sort_small(const LinkDesc* links, uint32_t n_links, hipStream_t s)
 {
-    k_sort_small<<<n_links, 1024, 0, s>>>(links);
+    // a workgroup per 64 keys for one link; several links share the chip
+    const dim3 g(n_links, n_links == 1 ? SORT_SMALL / 64u : 16u);
+    k_sort_keep<<<g, 1024, 0, s>>>(links);
+    k_sort_place<<<g, 1024, 0, s>>>(links);
     return hipGetLastError();
 }
 

@@ -920,7 +920,13 @@ int enqueue_close_tail(Engine* e, bool pack, uint64_t single_prefix, bool captur
     pm = begin();
     if (e->max_r <= DFS_MAX_ROWS) {
         // one depth-first launch for all levels
-        HIPCHK(e, launch_expand_dfs(la, e->max_r, s));
+        uint64_t table = 0;
+        uint32_t delta = 0;
+        for (uint32_t l = 0; l < e->n; l++) {
+            table = std::max(table, dfs_table_bytes(e->p[l].q, e->p[l].r));
+            delta = std::max(delta, e->p[l].delta);
+        }
+        HIPCHK(e, launch_expand_dfs(la, e->max_r, delta, table, s));
         end(pm, 3, 1);
     } else {
         HIPCHK(e, launch_expand0(la, s));
@@ -937,7 +943,7 @@ int enqueue_close_tail(Engine* e, bool pack, uint64_t single_prefix, bool captur
     pm = begin();
     HIPCHK(e, launch_sort_small(links, e->n, s));
     end(pm, 5, 1);
-    if (e->direct_mailbox) return SSD_OK;   // k_sort_small wrote the mailbox and advanced the clock
+    if (e->direct_mailbox) return SSD_OK;   // k_sort_place wrote the mailbox and advanced the clock
     if (e->gather_ctl) HIPCHK(e, launch_gather_ctl(links, e->n, e->at<Ctl>(e->L.ctl), s));
     HIPCHK(e, hipMemcpyAsync(e->mb_ctl, e->at<Ctl>(e->L.ctl), e->n * sizeof(Ctl), hipMemcpyDeviceToHost, s));
     if (pack) {
@@ -955,7 +961,7 @@ int enqueue_close_tail(Engine* e, bool pack, uint64_t single_prefix, bool captur
         HIPCHK(e, hipMemcpyAsync(e->mb_stage, e->hl[0].out, single_prefix * sizeof(SuperPointDev),
                                  hipMemcpyDeviceToHost, s));
     }
-    return SSD_OK;     // k_sort_small advanced every link's clock
+    return SSD_OK;     // k_sort_place advanced every link's clock
 }
 
 int enqueue_close(Engine* e, bool pack, uint64_t single_prefix)

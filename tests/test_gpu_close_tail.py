@@ -1,0 +1,84 @@
+"""The close's candidate expansion, final test and list ranking at the sizes
+where their kernels change path: rows and deltas of the queue walk and of the
+nested walk, waves with more full tuples than they stage, hot lists longer
+than the LDS copy, estimators of one to many loads per lane, lists around a
+workgroup's 64 keys and with hosts regained several times.  Every product
+against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import paper_1803_11036_amd as ssd
+import tracegen as tg
+from _parity import close_both, log, make_pair, scan_both
+
+pytestmark = pytest.mark.gpu
+
+
+def _pairs(seed, hosts, peers, key_bits, t=0):
+    """Slot t's pairs: `peers` peers for each of `hosts` distinct hosts below 2^key_bits (the same in every slot)."""
+    rng = np.random.default_rng(seed)
+    ip = rng.choice(1 << min(key_bits, 24), hosts, replace=False).astype(np.uint64)
+    if key_bits > 24:
+        ip = (ip * 2654435761) % (1 << 32)
+    rng = np.random.default_rng([seed, t])
+    p = np.empty((hosts * peers, 2), dtype=np.uint32)
+    p[:, 0] = np.repeat(ip, peers).astype(np.uint32)
+    p[:, 1] = rng.integers(0, 1 << 32, hosts * peers, dtype=np.uint32)
+    return p[rng.permutation(len(p))]
+
+
+CASES = [
+    # q, r, delta, key_bits, hosts, rehash
+    (8, 4, 4, 16, 120, False),       # crowded rows: hundreds of thousands of full tuples
+    (8, 4, 4, 16, 25, False),        # thousands of full tuples a workgroup, a few hundred keys
+    (12, 6, 5, 32, 150, False),      # the small trace's geometry, hosts regained by false tuples
+    (13, 6, 5, 32, 64, True),        # candidates with bits beyond the 32-bit key
+    (14, 5, 6, 32, 65, False),       # 64-bit words of candidates
+    (16, 6, 4, 32, 1025, True),      # the core link's geometry
+    (10, 7, 3, 25, 40, False),       # seven rows: four waves a workgroup
+    (9, 8, 3, 27, 20, False),        # eight rows
+    (9, 8, 1, 15, 30, True),         # one overlap bit a row
+    (12, 3, 6, 18, 200, False),      # three rows: no partial tuples
+    (12, 4, 7, 26, 100, False),      # delta above 6: the nested walk
+    (17, 3, 3, 20, 2100, True),      # hot lists longer than the LDS copy
+    (18, 6, 3, 30, 100, False),      # hot bits larger than the LDS: the nested walk
+    (5, 3, 3, 8, 6, False),          # rows of one word
+    (4, 7, 1, 9, 5, True),           # rows of half a word
+]
+
+
+@pytest.mark.parametrize("q,r,delta,key_bits,hosts,rehash", CASES)
+def test_expansion_against_oracle(q, r, delta, key_bits, hosts, rehash):
+    log(f"expansion q={q} r={r} delta={delta} hosts={hosts}")
+    g, o = make_pair(q, r, delta, 1024, 2, 16, tg.hash_tables(7), key_bits=key_bits, rehash=rehash,
+                     max_tuples=1 << 22)
+    for t in range(2):
+        scan_both(g, o, _pairs(q * 100 + r, hosts, 24, key_bits, t), t)
+        close_both(g, o)
+    g.destroy()
+
+
+@pytest.mark.parametrize("log2eta", [10, 11, 12, 13, 14, 15, 16])
+@pytest.mark.parametrize("r,delta,q", [(3, 8, 10), (6, 3, 8), (9, 2, 6)])
+def test_final_test_against_oracle(log2eta, r, delta, q):
+    """Lanes per tuple from 8 to 64, several loads a lane above 2^13; rows that fill one to three groups of three."""
+    log(f"final test eta=2^{log2eta} r={r}")
+    kb = (r - 2) * delta + q
+    eta = 1 << log2eta
+    g, o = make_pair(q, r, delta, eta, 1, 64, tg.hash_tables(3), key_bits=kb, max_tuples=1 << 20)
+    scan_both(g, o, _pairs(log2eta, 12, 150, kb), 0)
+    close_both(g, o)
+    g.destroy()
+
+
+@pytest.mark.parametrize("hosts", [0, 1, 63, 64, 65, 128, 1000])
+@pytest.mark.parametrize("limit", [8192, 64])
+def test_list_sizes(hosts, limit):
+    """Lists around a workgroup's 64 keys, also around the limit above which the multi-kernel sort takes them."""
+    log(f"list of {hosts} hosts, limit {limit}")
+    g, o = make_pair(16, 6, 4, 1024, 1, 16, tg.hash_tables(11), rehash=True)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SORT_BLOCK_LIMIT, limit)
+    scan_both(g, o, _pairs(hosts, hosts, 24, 32), 0)
+    res = close_both(g, o)
+    assert len(res) >= hosts * 0.9
+    g.destroy()
