@@ -303,18 +303,22 @@ int ssd_get_info(ssd_detector *d, ssd_info *out);
  *       scratch (included in ssd_query_sizes).  A scan call with fewer cell
  *       offsets per bin on average than SSD_TUNE_COUNTED_MIN_ITEMS (default
  *       2048 for detectors, 256 for batches, which scan each link once per
- *       slice) stores uncounted (the counted stores cost a workgroup per
- *       bin); it, a router
- *       merge into the detector, an advance-only close, a pass scan or a
- *       group call leaves the counters stale: the close reads the state,
- *       or, when every binned call of the slice was large, rebuilds the
- *       counters from it.  Large calls take the counted stores also while
+ *       slice) is too small for them (they cost a workgroup per bin).  While
+ *       the counters are exact and the state is large (above 256 MiB; links
+ *       of batches and members of groups: 64 MiB), a small call keeps them
+ *       exact pair by pair as long as the slice's small calls bring at most
+ *       one cell offset per 4096 bytes of state (batches and groups: 1024,
+ *       and at least 2^15 offsets); otherwise it stores uncounted.  An
+ *       uncounted call, a router merge into the detector, an advance-only
+ *       close or a pass scan leaves the counters stale: the close reads the
+ *       state, or, when every binned call of the slice was large, rebuilds
+ *       the counters from it.  Large calls take the counted stores also while
  *       the counters are stale (each touched 16-byte chunk is restamped
  *       once, faster than a byte store per offset when pairs repeat); the
  *       counters then stay stale until the rebuild.  Batches: the same for every link that can count
- *       (reading 1 if any link counts); a link scanned by the tile scan in a
- *       slice (fewer than 2^16 pairs in the call, or SSD_SCAN_PASSES) leaves
- *       its counters stale likewise. */
+ *       (reading 1 if any link counts); a link scanned uncounted by the tile
+ *       scan in a slice (fewer than 2^16 pairs in the call and not kept as
+ *       above, or SSD_SCAN_PASSES) leaves its counters stale likewise. */
 #define SSD_TUNE_COUNTED 10u
 #define SSD_TUNE_COUNTED_MIN_ITEMS 11u   /* counted scans: offsets per bin a call needs (default 2048, batches 256);
                                            the same bar, over bins of 2^18 cells, lets a binned call of a
@@ -430,9 +434,11 @@ int ssd_group_init(uint32_t max_members, void *scratch_dev, uint64_t scratch_byt
  * launch and one store launch per store kind over all of them (a member
  * whose pairs exceed its buffers takes part in several rounds); all others
  * share one tile-scan launch.  A member that keeps per-slot counters takes
- * the counted stores for a large call (each touched chunk restamped once),
- * its counters then untrusted until its own close rebuilds them: group
- * closes read every member's state. */
+ * the counted stores for a large call (each touched chunk restamped once) or
+ * the counted tile scan for a small one (SSD_TUNE_COUNTED); while they stay
+ * exact the group's close takes its R_k from them.  Group closes read the
+ * state of the other members, whose counters stay untrusted until their own
+ * close rebuilds them. */
 int ssd_group_scan(ssd_group *g, ssd_detector *const *members, uint32_t n, const uint32_t *pairs_dev,
                    const uint64_t *offsets_host, const uint64_t *slice_ids_host);
 

@@ -93,13 +93,16 @@ struct ScanArgs {
 };
 
 // persistent batched scan: one estimator window of one link and that link's
-// pairs, cut into tiles of `tile` pairs; windows are ordered by state address
+// pairs, cut into tiles; windows are ordered by state address
 struct ScanWindow {
-    uint32_t link, pad;
+    uint32_t link;
+    uint32_t counted;             // 1: the link's exact counters are kept (a window over its whole state)
     uint64_t start, n;            // the link's pairs [start, start + n) of the batch buffer
     uint64_t se_lo, se_hi;        // estimator window of the link
     uint64_t tile_base;           // tiles before this window
-    uint32_t stamp, pad2;         // the link's stamp for its open slice
+    uint32_t stamp;               // the link's stamp for its open slice
+    uint32_t slot;                // counted: the open slice mod k
+    uint64_t tile;                // pairs per tile
 };
 
 struct TileScanArgs {
@@ -108,7 +111,7 @@ struct TileScanArgs {
     const ScanWindow* wins;
     unsigned long long* counter;  // next tile; zero before the launch
     uint32_t n_wins;
-    uint64_t n_tiles, tile;
+    uint64_t n_tiles;
 };
 
 // binned scan, step 1: `pb` pairs per workgroup, their cell offsets sorted
@@ -217,6 +220,8 @@ hipError_t launch_prepare(const LinkDesc* links, uint32_t n_links, bool clear_ho
 hipError_t launch_advance(const LinkDesc* links, uint32_t n_links, hipStream_t s);
 hipError_t launch_gather_ctl(const LinkDesc* links, uint32_t n_links, Ctl* dst, hipStream_t s);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
+// one link's call, keeping its exact counters (the open slice's stamp, and slot mod k)
+hipError_t launch_scan_counted(const LinkDesc* link, const uint2* pairs, uint64_t n, uint32_t stamp, uint32_t slot, hipStream_t s);
 hipError_t launch_scan_tiles(const TileScanArgs& a, uint32_t blocks, hipStream_t s);
 // LDS words k_bin needs, and the launches of the two binned scan steps
 inline uint32_t bin_lds_words(uint32_t n_bins, uint32_t pb, uint32_t r) { return 2048u + n_bins + 1u + pb * r; }

@@ -275,8 +275,69 @@ __global__ __launch_bounds__(256) void k_scan(ScanArgs a)
                      a.se_lo, a.se_hi, (T)a.stamp);
 }
 
+// The same keeping exact counters exact, for calls with so few offsets that a
+// workgroup per bin costs more than they do: every cell's stamp is exchanged
+// by a compare-and-swap of its 32-bit word, and the one thread that changes it
+// moves its estimator's counters in memory (which slot, see k_apply_counted).
+// Six rows in flight.  Bound by random device-wide atomics, three for a cell
+// not yet stamped in the slice, 19 to 27 G/s: 5.8 G offsets/s.
+__device__ __forceinline__ void scan_pair_counted(const uint32_t* tab, uint2 pr, const LinkDesc* D, uint32_t stamp,
+                                                  uint32_t slot)
+{
+    const uint32_t q = D->q, delta = D->delta, log2eta = D->log2eta, r = D->r, k = D->k;
+    const uint32_t qmask = (1u << q) - 1u;
+    uint32_t* words = reinterpret_cast<uint32_t*>(D->state);
+    const uint32_t d = tab_hash(tab + 1024, pr.y) & ((1u << log2eta) - 1u);   // H1(oip)
+    const uint32_t h0 = tab_hash(tab, pr.x) & qmask;                          // RHFG[0](cip)
+    const uint32_t sh = (d & 3u) * 8u;
+    for (uint32_t i0 = 0; i0 < r; i0 += 6u) {
+        uint64_t se[6];
+        uint32_t w[6];
+#pragma unroll
+        for (uint32_t u = 0; u < 6; u++) {
+            const uint32_t i = min(i0 + u, r - 1u);
+            const uint32_t col = i == 0 ? h0 : ((shr32(pr.x, (i - 1) * delta) ^ h0) & qmask);
+            se[u] = ((uint64_t)i << q) | col;
+            w[u] = __hip_atomic_load(words + (((se[u] << log2eta) | d) >> 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        uint32_t left = (1u << min(6u, r - i0)) - 1u;          // rows not yet stamped
+        while (left) {
+            uint32_t was[6];
+#pragma unroll
+            for (uint32_t u = 0; u < 6; u++) {
+                was[u] = w[u];
+                if (!((left >> u) & 1u)) continue;
+                if (((w[u] >> sh) & 0xFFu) == stamp) left &= ~(1u << u);
+                else was[u] = atomicCAS(words + (((se[u] << log2eta) | d) >> 2), w[u], (w[u] & ~(0xFFu << sh)) | (stamp << sh));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 6; u++) {
+                if (!((left >> u) & 1u)) continue;
+                if (was[u] == w[u]) {                          // this thread's stamp
+                    const uint32_t b = (w[u] >> sh) & 0xFFu, age = (stamp + 255u - b) % 255u;
+                    atomicAdd(&D->counts[(uint64_t)slot * D->n_se + se[u]], 1u);
+                    if (b && age < k) atomicAdd(&D->counts[(uint64_t)(slot >= age ? slot - age : slot + k - age) * D->n_se + se[u]], ~0u);
+                    else atomicAdd(&D->counts[(uint64_t)k * D->n_se + se[u]], 1u);
+                    left &= ~(1u << u);
+                }
+                w[u] = was[u];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_scan_counted(const LinkDesc* D, const uint2* pairs, uint64_t n, uint32_t stamp,
+                                                      uint32_t slot)
+{
+    __shared__ uint32_t tab[2048];
+    for (uint32_t i = threadIdx.x; i < 2048u; i += 256u) tab[i] = D->tables[i];
+    __syncthreads();
+    const uint64_t stride = (uint64_t)gridDim.x * 256u;
+    for (uint64_t p = (uint64_t)blockIdx.x * 256u + threadIdx.x; p < n; p += stride) scan_pair_counted(tab, pairs[p], D, stamp, slot);
+}
+
 // Persistent scan over many links: workgroups pull tile numbers from a device
-// counter; a tile is `tile` pairs of one link restricted to one estimator
+// counter; a tile is some pairs of one link restricted to one estimator
 // window, found by binary search over the windows' tile prefix.  Windows are
 // ordered by state address and tiles are small, so the tiles in flight store
 // into a cache-sized range of state; a workgroup reloads the tabulation
@@ -300,13 +361,17 @@ __global__ __launch_bounds__(256) void k_scan_tiles(TileScanArgs a)
             else hi = mid;
         }
         const ScanWindow W = a.wins[lo];
-        const uint64_t first = W.start + (t - W.tile_base) * a.tile;
-        const uint64_t last = min(first + a.tile, W.start + W.n);
+        const uint64_t first = W.start + (t - W.tile_base) * W.tile;
+        const uint64_t last = min(first + W.tile, W.start + W.n);
         const LinkDesc* D = a.links + W.link;
         if (W.link != loaded) {
             for (uint32_t i = threadIdx.x; i < 2048u; i += 256u) tab[i] = D->tables[i];
             __syncthreads();
             loaded = W.link;
+        }
+        if (W.counted) {
+            for (uint64_t p = first + threadIdx.x; p < last; p += 256u) scan_pair_counted(tab, a.pairs[p], D, W.stamp, W.slot);
+            continue;
         }
         const uint32_t q = D->q, delta = D->delta, log2eta = D->log2eta;
         uint8_t* state = D->state;
@@ -2346,6 +2411,12 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s)
 {
     if (a.cell16) k_scan<uint16_t><<<grid_for(a.n, 256, 256 * 16), 256, 0, s>>>(a);
     else k_scan<uint8_t><<<grid_for(a.n, 256, 256 * 16), 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_scan_counted(const LinkDesc* link, const uint2* pairs, uint64_t n, uint32_t stamp, uint32_t slot, hipStream_t s)
+{
+    k_scan_counted<<<grid_for(n, 256, 2048), 256, 0, s>>>(link, pairs, n, stamp, slot);
     return hipGetLastError();
 }
 

@@ -174,6 +174,22 @@ constexpr uint32_t PHASE_SCAN_TILES = 10;
 // go to the persistent tile scan, since the binned stores cost workgroups
 // per bin whatever the call's size)
 constexpr uint64_t BATCH_BINNED_MIN_PAIRS = 1ull << 16;
+// Links of a batch and members of a group with fewer pairs than the binned
+// scan takes, that keep exact counters: calls of at least COUNTED_MIN_OFFSETS
+// offsets into states above COUNTED_TILES_ABOVE are scanned in counted tiles
+// where direct_call allows it (a smaller state is read at the close in less
+// than the launches around it take).
+constexpr uint64_t COUNTED_TILES_ABOVE = 64ull << 20;
+constexpr uint64_t COUNTED_MIN_OFFSETS = 1ull << 15;
+constexpr uint64_t COUNTED_TILE_PAIRS = 256;      // pairs per tile there (a pair a thread)
+// State bytes per offset taken directly: batches and groups mostly scan a
+// slice in one call (24 links of 4K to 160K pairs, 8.8 GB of state, in one
+// batch: 0.76 ms per slice without a limit and 0.99 at 2048, against 2.28 with
+// every state read); a single detector's slice may bring many more calls, all
+// for nothing once one of them drops the counters, so a fifth of the state's
+// read is all it spends.
+constexpr uint64_t TILES_DIRECT_BYTES = 1024;
+constexpr uint64_t SINGLE_DIRECT_BYTES = 4096;
 // group members scanned binned (in the multi-member launches): at least this
 // many pairs in the call, whatever the state's size (a member whose scan mode
 // is SSD_SCAN_PASSES keeps the tile scan)
@@ -402,12 +418,13 @@ struct Engine {
     std::vector<uint8_t> counting, count_valid, count_rebuild;
     std::vector<uint64_t> detect_prefix;   // the hot detection wave prefix on the device
     uint64_t counted_bin_bytes = DEFAULT_COUNTED_BIN_BYTES;   // bin size request of counted scans
-    uint64_t counted_min_items = DEFAULT_COUNTED_MIN_ITEMS;   // offsets per bin a call needs to count
+    uint64_t counted_min_items = DEFAULT_COUNTED_MIN_ITEMS;   // offsets per bin a call needs to count through the bitmap
+    std::vector<uint64_t> direct;          // per link: offsets of this slice's calls that kept the counters directly
     std::vector<uint8_t> count_small;      // a call of this slice stored uncounted for being small
     std::vector<uint8_t> last_mode;        // hot detection of the last close: 0 state, 1 counters, 2 rebuilt
     std::vector<uint64_t> bin_req;         // per link: bin size request of its counted scans (0: counted_bin_bytes)
     std::vector<uint8_t> last_csh;         // per link: bin shift of its last counted binned call (0: none)
-    uint32_t* cl_pinned = nullptr;         // staging of the counted-link list (2n + 1 words)
+    uint32_t* cl_pinned = nullptr;         // staging of the counted-link list (2n + 1 words, n up to MAX_LINKS)
     hipEvent_t cl_done = nullptr;          // its last copy has run
     std::vector<LinkDesc> hl;          // host copies of the device descriptors
     std::vector<uint32_t> tables;      // n x 2048
@@ -635,6 +652,7 @@ int engine_init(Engine* e, const ssd_params* p, uint32_t n, const uint32_t* tabl
     e->count_valid.assign(n, 0);
     e->count_rebuild.assign(n, 0);
     e->count_small.assign(n, 0);
+    e->direct.assign(n, 0);
     e->last_mode.assign(n, 0);
     e->bin_req.assign(n, 0);
     e->last_csh.assign(n, 0);
@@ -709,6 +727,27 @@ BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_byt
     c.bp = bin_plan(e->p[l], c.counted ? 1ull << c.csh : c.marked ? MARKED16_BIN_BYTES : bin_bytes);
     c.seg = (uint64_t)c.bp.pb * e->p[l].r;
     return c;
+}
+
+// Whether a small call of n pairs of link l keeps the link's exact counters by
+// the direct counted scan (k_scan_counted, or counted tiles): while the
+// slice's calls so taken, this one included, have at most one offset per
+// `bytes` of a state above `above`.  Dropping the counters costs the close a
+// read of the whole state (5 TB/s); the direct scan takes as long for an
+// offset (5.8 G/s) as that read for 850 bytes.
+bool direct_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bytes, uint64_t above)
+{
+    const uint64_t state = state_bytes_of(e->p[l]);
+    return e->counting[l] && e->count_valid[l] && state > above && e->direct[l] + n * e->p[l].r <= state / bytes;
+}
+
+// The same for a link of a batch or a member of a group, whose calls below
+// binned_min pairs go to the tile scan, and from there on are binned and
+// stored uncounted where they are too small for the counted stores.
+bool direct_tiles(const Engine* e, uint32_t l, uint64_t n, uint64_t binned_min)
+{
+    return n * e->p[l].r >= COUNTED_MIN_OFFSETS && direct_call(e, l, n, TILES_DIRECT_BYTES, COUNTED_TILES_ABOVE) &&
+           (n < binned_min || !binned_call(e, l, n, DEFAULT_BIN_BYTES).exact);
 }
 
 // Staging of the binned scan: the binning workgroups' offset segments (4 *
@@ -870,7 +909,7 @@ int enqueue_close_head(Engine* e)
             HIPCHK(e, launch_count(links + ids[0], e->hl[ids[0]].n_se, s));
         } else {
             if (!e->cl_pinned) {
-                HIPCHK(e, hipHostMalloc(reinterpret_cast<void**>(&e->cl_pinned), (2ull * n + 1) * 4, hipHostMallocDefault));
+                HIPCHK(e, hipHostMalloc(reinterpret_cast<void**>(&e->cl_pinned), (2ull * MAX_LINKS + 1) * 4, hipHostMallocDefault));
                 HIPCHK(e, hipEventCreateWithFlags(&e->cl_done, hipEventDisableTiming));
             } else {
                 HIPCHK(e, hipEventSynchronize(e->cl_done));     // the last copy out of the staging has run
@@ -896,6 +935,7 @@ int enqueue_close_head(Engine* e)
         e->count_valid[l] = mode[l] != 0;
         e->count_rebuild[l] = 0;
         e->count_small[l] = 0;
+        e->direct[l] = 0;
     }
     return SSD_OK;
 }
@@ -1077,6 +1117,7 @@ int enqueue_advance_only(Engine* e)
     e->count_valid[0] = 0;            // the next slot's counters are not zeroed
     e->count_rebuild[0] = 0;
     e->count_small[0] = 0;
+    e->direct[0] = 0;
     LinkDesc* links = e->dev_links();
     HIPCHK(e, launch_prepare(links, e->n, false, s));
     DetectArgs da{};
@@ -1221,6 +1262,22 @@ bool scans_binned(const ssd_detector* d)
     const LinkDesc& D = d->D();
     const uint64_t state_bytes = (D.n_se << D.log2eta) << D.cell16;
     return d->scan_mode == SSD_SCAN_BINNED || (d->scan_mode == SSD_SCAN_AUTO && state_bytes > AUTO_BINNED_ABOVE);
+}
+
+// A call too small for the counted stores that keeps exact counters directly.
+bool scans_direct(const ssd_detector* d, uint64_t n)
+{
+    return scans_binned(d) && direct_call(&d->e, 0, n, SINGLE_DIRECT_BYTES, AUTO_BINNED_ABOVE) && !binned_call(&d->e, 0, n, d->bin_bytes).exact;
+}
+
+int enqueue_direct_scan(Engine* e, const uint2* pairs, uint64_t n)
+{
+    const LinkDesc& D = e->hl[0];
+    e->direct[0] += n * D.r;
+    PhaseMark pm = phase_begin(e);
+    HIPCHK(e, launch_scan_counted(e->dev_links(), pairs, n, stamp_of(e->clock, false), (uint32_t)(e->clock % D.k), e->stream));
+    phase_end(e, pm, 0, 1);
+    return SSD_OK;
 }
 
 // Pass-window scan (k_scan): passes over estimator windows of about
@@ -1407,6 +1464,19 @@ void autotune_collect(ssd_batch* b)
     }
 }
 
+// The store kind of a link in the multi-link launches, its workgroups and LDS,
+// and the launch of one kind.
+uint32_t store_lds(const ApplyArgs& y)
+{
+    return y.counts ? (uint32_t)counted_lds_bytes(y.bin_shift, y.log2eta, y.k) : 0u;
+}
+uint32_t store_kind(const ApplyArgs& y) { return !y.counts ? 11u : store_lds(y) <= COUNTED_LDS_PAIR ? 10u : 12u; }
+uint32_t store_workgroups(const ApplyArgs& y) { return y.counts ? apply_counted_workgroups(y) : apply_workgroups(y); }
+hipError_t launch_stores(const MultiApplyArgs& m, uint32_t kind, uint32_t total_wg, uint32_t lds, hipStream_t s)
+{
+    return kind == 11u ? launch_apply_multi(m, total_wg, s) : launch_apply_counted_multi(m, total_wg, lds, s);
+}
+
 // The binned scan of the batch's links `links` (each with enough pairs in
 // this call; offsets as in ssd_batch_scan).  The links are packed, in order,
 // into groups whose staging fits the batch's bin buffers; a group takes one
@@ -1502,20 +1572,15 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
         // stores: counted (the links whose LDS lets two workgroups share a
         // compute unit, then the others: a launch's LDS is its largest
         // link's), then uncounted
-        auto kind_of = [](const ApplyArgs& y) {
-            if (!y.counts) return 11u;
-            return counted_lds_bytes(y.bin_shift, y.log2eta, y.k) <= COUNTED_LDS_PAIR ? 10u : 12u;
-        };
         for (uint32_t kind : {10u, 12u, 11u}) {
             Launch L{kind, na, 0, np_words, 0, 0};
             for (const ApplyArgs& y : aa) {
-                if (kind_of(y) != kind) continue;
+                if (store_kind(y) != kind) continue;
                 ha[na++] = y;
                 hp[np_words + L.count] = L.total_wg;
                 L.count++;
-                L.total_wg += kind == 11u ? apply_workgroups(y) : apply_counted_workgroups(y);
-                if (kind != 11u)
-                    L.lds = std::max<uint32_t>(L.lds, (uint32_t)counted_lds_bytes(y.bin_shift, y.log2eta, y.k));
+                L.total_wg += store_workgroups(y);
+                L.lds = std::max(L.lds, store_lds(y));
             }
             if (!L.count) continue;
             hp[np_words + L.count] = L.total_wg;
@@ -1535,8 +1600,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
             PhaseMark pm = phase_begin(e);
             if (L.kind >= 10u) {
                 MultiApplyArgs m{da + L.first, dp + L.pre, L.count};
-                HIPCHK(e, L.kind != 11u ? launch_apply_counted_multi(m, L.total_wg, L.lds, e->stream)
-                                        : launch_apply_multi(m, L.total_wg, e->stream));
+                HIPCHK(e, launch_stores(m, L.kind, L.total_wg, L.lds, e->stream));
                 phase_end(e, pm, 0, 1);
             } else {
                 MultiBinArgs m{db + L.first, dp + L.pre, L.count};
@@ -1565,6 +1629,7 @@ struct ssd_group {
     // a close begun and not yet ended: its members and its completion
     bool pending = false;
     std::vector<ssd_detector*> pending_members;
+    std::vector<uint8_t> pending_mode;  // how its hot detection took each member's R_k
     hipEvent_t done = nullptr;
     // arguments of the binned members' multi-link launches, staged in pinned
     // memory (two buffers, each reused once its last copy has run)
@@ -1657,6 +1722,7 @@ int group_bind(ssd_group* g, ssd_detector* const* m, uint32_t n)
     e->count_valid.assign(n, 0);
     e->count_rebuild.assign(n, 0);
     e->count_small.assign(n, 0);
+    e->direct.assign(n, 0);
     e->last_mode.assign(n, 0);
     e->bin_req.assign(n, 0);
     e->last_csh.assign(n, 0);
@@ -1815,6 +1881,7 @@ int ssd_scan_slice(ssd_detector* d, const uint32_t* pairs_dev, uint64_t n, uint6
     Engine* e = &d->e;
     int rc = scan_checks(d, pairs_dev, n, slice_id);
     if (rc || n == 0) return rc;
+    if (scans_direct(d, n)) return enqueue_direct_scan(e, reinterpret_cast<const uint2*>(pairs_dev), n);
     if (scans_binned(d))
         return enqueue_binned_scan(e, 0, reinterpret_cast<const uint2*>(pairs_dev), n, d->bin_bytes, d->apply_segments,
                                    engine_bins(e));
@@ -1830,7 +1897,9 @@ int ssd_scan_slice_noalloc(ssd_detector* d, const uint32_t* pairs_dev, uint64_t 
     // no phase timing: its events would be created on first use
     const bool timing = e->timing;
     e->timing = false;
-    if (scans_binned(d)) {
+    if (scans_direct(d, n)) {
+        rc = enqueue_direct_scan(e, reinterpret_cast<const uint2*>(pairs_dev), n);           // no staging
+    } else if (scans_binned(d)) {
         // the binning's staging in this device's static array, looked up at
         // ssd_init_detector; one step for the whole call
         uint8_t* base = noalloc_scratch(e->device);
@@ -2114,6 +2183,7 @@ int ssd_import_state(ssd_detector* d, const void* blob_host, uint64_t n)
     e->count_valid[0] = 0;
     e->count_rebuild[0] = 0;
     e->count_small[0] = 0;
+    e->direct[0] = 0;
     e->have_last = false;
     e->results[0].clear();
     return SSD_OK;
@@ -2355,20 +2425,28 @@ int ssd_batch_scan(ssd_batch* b, const uint32_t* pairs_dev, const uint64_t* offs
     // separate detector would); the others share one persistent tile scan
     std::vector<uint32_t> binned;
     if (b->scan_mode != SSD_SCAN_PASSES && e->L.bin_items_words) {
-        for (uint32_t l = 0; l < e->n; l++)
-            if (offsets_host[l + 1] - offsets_host[l] >= BATCH_BINNED_MIN_PAIRS) binned.push_back(l);
+        for (uint32_t l = 0; l < e->n; l++) {
+            const uint64_t np = offsets_host[l + 1] - offsets_host[l];
+            if (np >= BATCH_BINNED_MIN_PAIRS && !direct_tiles(e, l, np, BATCH_BINNED_MIN_PAIRS)) binned.push_back(l);
+        }
     }
     auto is_binned = [&](uint32_t l) { return std::find(binned.begin(), binned.end(), l) != binned.end(); };
     // windows of every other link's state, ordered by address; tiles are implicit
-    struct Win { uint64_t at; uint32_t link; uint64_t lo, hi; };
+    struct Win { uint64_t at; uint32_t link; uint64_t lo, hi; uint32_t counted; };
     std::vector<Win> wins;
     for (uint32_t l = 0; l < e->n; l++) {
         if (offsets_host[l + 1] == offsets_host[l] || is_binned(l)) continue;
-        e->count_valid[l] = 0;             // the tile scan stores without counting
         const LinkDesc& D = e->hl[l];
+        const uint64_t np = offsets_host[l + 1] - offsets_host[l];
+        if (b->scan_mode != SSD_SCAN_PASSES && direct_tiles(e, l, np, BATCH_BINNED_MIN_PAIRS)) {
+            e->direct[l] += np * e->p[l].r;
+            wins.push_back({e->L.link[l].state_off, l, 0, D.n_se, 1u});
+            continue;
+        }
+        e->count_valid[l] = 0;             // the tile scan stores without counting
         const uint64_t per = pass ? std::max<uint64_t>(1, pass / D.eta) : D.n_se;
         for (uint64_t lo = 0; lo < D.n_se; lo += per)
-            wins.push_back({e->L.link[l].state_off + lo * D.eta, l, lo, std::min(lo + per, D.n_se)});
+            wins.push_back({e->L.link[l].state_off + lo * D.eta, l, lo, std::min(lo + per, D.n_se), 0u});
     }
     if (wins.size() > MAX_WINDOWS) return fail(SSD_E_PARAM, "scan pass window too small: %zu windows", wins.size());
     if (wins.empty()) cand = -1;
@@ -2387,16 +2465,18 @@ int ssd_batch_scan(ssd_batch* b, const uint32_t* pairs_dev, const uint64_t* offs
         for (size_t i = 0; i < wins.size(); i++) {
             const Win& w = wins[i];
             ScanWindow& W = ws[i];
+            W = ScanWindow{};
             W.link = w.link;
-            W.pad = 0;
             W.start = offsets_host[w.link];
             W.n = offsets_host[w.link + 1] - W.start;
             W.se_lo = w.lo;
             W.se_hi = w.hi;
             W.tile_base = tiles;
             W.stamp = stamp_of(e->clock, false);
-            W.pad2 = 0;
-            tiles += (W.n + tile - 1) / tile;
+            W.counted = w.counted;
+            W.slot = (uint32_t)(e->clock % e->hl[w.link].k);
+            W.tile = w.counted ? std::min(tile, COUNTED_TILE_PAIRS) : tile;
+            tiles += (W.n + W.tile - 1) / W.tile;
         }
         unsigned long long* dcounter = e->at<unsigned long long>(e->L.tiles);
         HIPCHK(e, hipMemcpyAsync(dcounter, counter, 8 + wins.size() * sizeof(ScanWindow), hipMemcpyHostToDevice,
@@ -2410,7 +2490,6 @@ int ssd_batch_scan(ssd_batch* b, const uint32_t* pairs_dev, const uint64_t* offs
         a.counter = dcounter;
         a.n_wins = (uint32_t)wins.size();
         a.n_tiles = tiles;
-        a.tile = tile;
         hipEvent_t ta = nullptr, tb = nullptr;
         if (cand >= 0) {
             HIPCHK(e, hipEventCreate(&ta));
@@ -2654,12 +2733,14 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
     // the others (as the links of a batch: XCD-local stores beat pass windows
     // for such calls whatever the state's size) -- when they were set up on
     // the group's stream, so that the group's close stays ordered after them
-    auto binned = [&](uint32_t i) {
+    std::vector<uint8_t> in_bins(n, 0);
+    for (uint32_t i = 0; i < n; i++) {
         const ssd_detector* m = members[i];
-        if (m->e.stream != e->stream) return false;
         const uint64_t np = offsets_host[i + 1] - offsets_host[i];
-        return m->scan_mode != SSD_SCAN_PASSES && np >= GROUP_BINNED_MIN_PAIRS;
-    };
+        if (m->e.stream != e->stream || m->scan_mode == SSD_SCAN_PASSES) continue;
+        in_bins[i] = np >= GROUP_BINNED_MIN_PAIRS && !direct_tiles(&m->e, 0, np, GROUP_BINNED_MIN_PAIRS);
+    }
+    auto binned = [&](uint32_t i) { return in_bins[i] != 0; };
     // windows of every other member's state (its own pass window), in member order
     std::vector<ScanWindow> ws;
     uint64_t tiles = 0;
@@ -2669,8 +2750,11 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         const uint64_t np = offsets_host[i + 1] - offsets_host[i];
         if (!np || binned(i)) continue;
         const LinkDesc& D = e->hl[i];
+        const uint32_t counted = members[i]->scan_mode != SSD_SCAN_PASSES && direct_tiles(&members[i]->e, 0, np, GROUP_BINNED_MIN_PAIRS) ? 1u : 0u;
+        if (counted) members[i]->e.direct[0] += np * D.r;
+        else members[i]->e.count_valid[0] = 0;               // the tile scan stores without counting
         const uint64_t pass = members[i]->pass_bytes;
-        const uint64_t per = pass ? std::max<uint64_t>(1, pass / D.eta) : D.n_se;
+        const uint64_t per = pass && !counted ? std::max<uint64_t>(1, pass / D.eta) : D.n_se;
         for (uint64_t lo = 0; lo < D.n_se; lo += per) {
             ScanWindow W{};
             W.link = i;
@@ -2680,7 +2764,10 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
             W.se_hi = std::min(lo + per, D.n_se);
             W.tile_base = tiles;
             W.stamp = stamp_of(members[i]->e.clock, false);
-            tiles += (np + tile - 1) / tile;
+            W.counted = counted;
+            W.slot = (uint32_t)(members[i]->e.clock % D.k);
+            W.tile = counted ? COUNTED_TILE_PAIRS : tile;
+            tiles += (np + W.tile - 1) / W.tile;
             ws.push_back(W);
         }
     }
@@ -2707,20 +2794,18 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         a.counter = dcounter;
         a.n_wins = (uint32_t)n_wins;
         a.n_tiles = tiles;
-        a.tile = tile;
         PhaseMark pm = phase_begin(e);
         HIPCHK(e, launch_scan_tiles(a, (uint32_t)std::min<uint64_t>(g->scan_blocks, tiles), e->stream));
         phase_end(e, pm, PHASE_SCAN_TILES, 1);
     }
-    for (uint32_t i = 0; i < n; i++) members[i]->e.count_valid[0] = 0;   // group scans leave the counters stale
     // the binned members: rounds of one binning launch and one store launch
     // per kind over all of them, each member binning into its own staging (a
     // member whose pairs exceed its staging takes part in several rounds); a
     // member whose bins are too large for packed offsets is scanned alone.
-    // A member that keeps per-slot counters takes the counted stores for a
-    // large call (binned_call); its counters stay untrusted (the group's
-    // close reads every member's state; the member's own close rebuilds them
-    // before it counts again).
+    // A member that keeps per-slot counters takes the counted stores, which
+    // keep exact counters exact (binned_call); stale ones stay untrusted: the
+    // group's close reads that member's state (the member's own close
+    // rebuilds them before it counts again).
     struct Binned {
         ssd_detector* m;
         BinnedCall c;
@@ -2762,25 +2847,15 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         uint8_t* host = static_cast<uint8_t*>(g->mb_pinned[buf]);
         BinArgs* hb = reinterpret_cast<BinArgs*>(host);
         ApplyArgs* ha = reinterpret_cast<ApplyArgs*>(host + app_region);
-        uint32_t* hp = reinterpret_cast<uint32_t*>(host + pre_region);    // [binning prefix][3 store prefixes]
-        // the round's members by store kind: counted whose LDS lets two
-        // workgroups share a compute unit (0), uncounted (1), counted needing
-        // more LDS (2); a launch per kind, with its own workgroup prefix
-        auto kind_of = [&](const Binned& b) -> uint32_t {
-            if (!b.c.counted) return 1u;
-            const LinkDesc& D = b.m->e.hl[0];
-            return counted_lds_bytes(b.c.bp.shift, D.log2eta, D.k) <= COUNTED_LDS_PAIR ? 0u : 2u;
-        };
-        std::stable_sort(round.begin(), round.end(),
-                         [&](uint32_t a, uint32_t c) { return kind_of(bm[a]) < kind_of(bm[c]); });
-        uint32_t bin_wg = 0, app_wg[3] = {0, 0, 0}, kcount[3] = {0, 0, 0}, lds[3] = {0, 0, 0};
-        for (uint32_t x = 0; x < cnt; x++) kcount[kind_of(bm[round[x]])]++;
-        const uint32_t kfirst[3] = {0, kcount[0], kcount[0] + kcount[1]};
+        uint32_t* hp = reinterpret_cast<uint32_t*>(host + pre_region);    // [binning prefix][a prefix per store kind]
+        // the round's members by store kind: a launch per kind, with its own
+        // workgroup prefix
+        std::vector<std::pair<BinArgs, ApplyArgs>> args(cnt);
         for (uint32_t x = 0; x < cnt; x++) {
             Binned& b = bm[round[x]];
             const uint64_t np = std::min(b.chunk, b.n - b.done);
-            BinArgs ba{};
-            ApplyArgs aa{};
+            BinArgs& ba = args[x].first;
+            ApplyArgs& aa = args[x].second;
             binned_args(&b.m->e, 0, b.c, b.bb.items, b.bb.table, b.m->apply_segments, &ba, &aa);
             ba.pairs = reinterpret_cast<const uint2*>(pairs_dev) + b.begin + b.done;
             ba.n = np;
@@ -2788,17 +2863,30 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
             aa.blocks = ba.blocks;
             aa.parts = (aa.blocks + aa.per_part - 1) / aa.per_part;
             b.done += np;
-            hb[x] = ba;
-            ha[x] = aa;
+        }
+        std::stable_sort(args.begin(), args.end(),
+                         [](const auto& x, const auto& y) { return store_kind(x.second) < store_kind(y.second); });
+        struct Stores { uint32_t kind, first, count, total_wg, lds; };
+        std::vector<Stores> stores;
+        uint32_t bin_wg = 0, np_words = cnt + 1;
+        for (uint32_t x = 0; x < cnt; x++) {
+            hb[x] = args[x].first;
+            ha[x] = args[x].second;
             hp[x] = bin_wg;
-            bin_wg += bin_workgroups(ba);
-            const uint32_t kd = kind_of(b);
-            hp[(kd + 1) * (cnt + 1) + (x - kfirst[kd])] = app_wg[kd];
-            app_wg[kd] += kd == 1u ? apply_workgroups(aa) : apply_counted_workgroups(aa);
-            if (kd != 1u) lds[kd] = std::max<uint32_t>(lds[kd], (uint32_t)counted_lds_bytes(aa.bin_shift, aa.log2eta, aa.k));
+            bin_wg += bin_workgroups(hb[x]);
+            const uint32_t kd = store_kind(ha[x]);
+            if (stores.empty() || stores.back().kind != kd) {
+                if (!stores.empty()) hp[np_words++] = stores.back().total_wg;
+                stores.push_back({kd, x, 0, 0, 0});
+            }
+            Stores& st = stores.back();
+            hp[np_words++] = st.total_wg;
+            st.count++;
+            st.total_wg += store_workgroups(ha[x]);
+            st.lds = std::max(st.lds, store_lds(ha[x]));
         }
         hp[cnt] = bin_wg;
-        for (uint32_t kd = 0; kd < 3; kd++) hp[(kd + 1) * (cnt + 1) + kcount[kd]] = app_wg[kd];
+        hp[np_words++] = stores.back().total_wg;
         HIPCHK(e, hipMemcpyAsync(dev, host, multi_args_bytes(g->max_members), hipMemcpyHostToDevice, e->stream));
         HIPCHK(e, hipEventRecord(g->mb_done[buf], e->stream));
         g->mb_used[buf] = true;
@@ -2809,12 +2897,11 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         HIPCHK(e, launch_bin_multi(MultiBinArgs{reinterpret_cast<const BinArgs*>(dev), dp, cnt}, bin_wg, e->stream));
         for (uint32_t x = 0; x < cnt; x++) phase_end(&bm[round[x]].m->e, pm[x], PHASE_SCAN_BIN, 1);
         for (uint32_t x = 0; x < cnt; x++) pm[x] = phase_begin(&bm[round[x]].m->e);
-        for (uint32_t kd = 0; kd < 3; kd++) {
-            if (!kcount[kd]) continue;
-            const MultiApplyArgs ma{reinterpret_cast<const ApplyArgs*>(dev + app_region) + kfirst[kd],
-                                    dp + (kd + 1) * (cnt + 1), kcount[kd]};
-            if (kd == 1u) HIPCHK(e, launch_apply_multi(ma, app_wg[kd], e->stream));
-            else HIPCHK(e, launch_apply_counted_multi(ma, app_wg[kd], lds[kd], e->stream));
+        uint32_t pre_at = cnt + 1;
+        for (const Stores& st : stores) {
+            const MultiApplyArgs ma{reinterpret_cast<const ApplyArgs*>(dev + app_region) + st.first, dp + pre_at, st.count};
+            HIPCHK(e, launch_stores(ma, st.kind, st.total_wg, st.lds, e->stream));
+            pre_at += st.count + 1;
         }
         for (uint32_t x = 0; x < cnt; x++) phase_end(&bm[round[x]].m->e, pm[x], 0, 1);
     }
@@ -2833,12 +2920,17 @@ int ssd_group_close_begin(ssd_group* g, ssd_detector* const* members, uint32_t n
     for (uint32_t i = 0; i < n; i++)
         if (close_pending(members[i])) return fail(SSD_E_ORDER, "member %u has a close pending", i);
     if (!g->done) HIPCHK(e, hipEventCreateWithFlags(&g->done, hipEventDisableTiming));
-    // a group's close reads every member's state (served streams' calls are
-    // mostly too small to count; counted group closes measured slower) and
-    // zeroes no member's next slot
+    // members with exact counters close from them; the others' states are
+    // read, and their next slot is not zeroed
     for (uint32_t i = 0; i < n; i++) {
-        members[i]->e.count_valid[0] = 0;
-        members[i]->e.count_rebuild[0] = 0;
+        Engine& me = members[i]->e;
+        e->counting[i] = me.counting[0];
+        e->count_valid[i] = me.counting[0] && me.count_valid[0];
+        e->count_rebuild[i] = 0;
+        me.count_valid[0] = e->count_valid[i];
+        me.count_rebuild[0] = 0;
+        me.count_small[0] = 0;
+        me.direct[0] = 0;
     }
     rc = enqueue_close(e, true, 0);
     if (rc) return rc;
@@ -2847,6 +2939,7 @@ int ssd_group_close_begin(ssd_group* g, ssd_detector* const* members, uint32_t n
     // the lists are collected
     g->pending = true;
     g->pending_members.assign(members, members + n);
+    g->pending_mode.assign(e->last_mode.begin(), e->last_mode.begin() + n);
     for (uint32_t i = 0; i < n; i++) {
         members[i]->group_pending = true;
         members[i]->e.clock++;
@@ -2883,7 +2976,7 @@ int ssd_group_close_end(ssd_group* g, ssd_super_point* out_host, uint64_t cap, u
         me.results[0] = e->results[i];
         me.status[0] = e->status[i];
         me.last[0] = e->last[i];
-        me.last_mode[0] = e->last_mode[i];
+        me.last_mode[0] = g->pending_mode[i];
         me.have_last = true;
         if (counts_host) counts_host[i] = e->results[i].size();
         if (status_host) status_host[i] = e->status[i];
