@@ -763,6 +763,23 @@ BinBufs engine_bins(const Engine* e)
             e->L.bin_table_words};
 }
 
+// Pairs per binning workgroup of a call of n pairs scanned in launches of its
+// own: a whole number of rounds over the compute units, of at least
+// MIN_BIN_PAIRS pairs a workgroup, where the staging holds the plan (the
+// largest workgroups left 33 of 256 compute units at work on a 200K-pair call,
+// and a quarter of them in the second round of a 2M-pair one).
+void bin_fill(BinnedCall& c, uint32_t r, uint64_t n, const BinBufs& bb)
+{
+    constexpr uint64_t CUS = 256, MIN_BIN_PAIRS = 2048;
+    const uint64_t most = (n + c.bp.pb - 1) / c.bp.pb;
+    const uint64_t rounds = (most + CUS - 1) / CUS;
+    const uint64_t blocks = std::max<uint64_t>(1, std::min(rounds * CUS, (n + MIN_BIN_PAIRS - 1) / MIN_BIN_PAIRS));
+    const uint64_t pb = (n + blocks - 1) / blocks;
+    if (pb >= c.bp.pb || blocks * pb * r > bb.items_words || blocks * (c.bp.n_bins + 1) > bb.table_words) return;
+    c.bp.pb = (uint32_t)pb;
+    c.seg = pb * r;
+}
+
 // The counter bookkeeping of a binned call of link l: after stores that do
 // not keep the counters exact, the counters are stale (rebuilt at the close
 // after a large call).
@@ -824,7 +841,8 @@ void binned_args(const Engine* e, uint32_t l, const BinnedCall& c, uint32_t* ite
 int enqueue_binned_scan(Engine* e, uint32_t l, const uint2* pairs, uint64_t n, uint64_t bin_bytes, uint32_t segs,
                         const BinBufs& bb)
 {
-    const BinnedCall c = binned_call(e, l, n, bin_bytes);
+    BinnedCall c = binned_call(e, l, n, bin_bytes);
+    bin_fill(c, e->p[l].r, n, bb);
     const bool counted = c.counted;
     binned_count_state(e, l, c);
     const BinPlan bp = c.bp;
@@ -1906,6 +1924,8 @@ int ssd_scan_slice_noalloc(ssd_detector* d, const uint32_t* pairs_dev, uint64_t 
         const BinnedCall c = binned_call(e, 0, n, d->bin_bytes);
         const uint64_t blocks = (n + c.bp.pb - 1) / c.bp.pb;
         const uint64_t items = align_up(blocks * c.seg * 4), table = (uint64_t)(c.bp.n_bins + 1) * blocks * 4;
+        // what the segments leave of the array is the table's (smaller binning workgroups need more of it)
+        const uint64_t table_words = (SSD_NOALLOC_SCRATCH_BYTES - std::min<uint64_t>(items, SSD_NOALLOC_SCRATCH_BYTES)) / 4;
         if (!base) rc = fail(SSD_E_STATE, "no static scratch for device %d", e->device);
         else if (items + table > SSD_NOALLOC_SCRATCH_BYTES)
             rc = fail(SSD_E_NOMEM, "a binned scan of %llu pairs needs %llu bytes of staging, the static scratch holds "
@@ -1915,7 +1935,7 @@ int ssd_scan_slice_noalloc(ssd_detector* d, const uint32_t* pairs_dev, uint64_t 
             rc = enqueue_binned_scan(e, 0, reinterpret_cast<const uint2*>(pairs_dev), n, d->bin_bytes,
                                      d->apply_segments,
                                      {reinterpret_cast<uint32_t*>(base), reinterpret_cast<uint32_t*>(base + items),
-                                      blocks * c.seg, (uint64_t)(c.bp.n_bins + 1) * blocks});
+                                      blocks * c.seg, table_words});
     } else {
         rc = enqueue_pass_scan(d, reinterpret_cast<const uint2*>(pairs_dev), n);     // no staging
     }
