@@ -190,6 +190,7 @@ struct DetectArgs {
     uint32_t n_links;
     uint64_t total;               // waves launched
     uint32_t expire_only;         // link 0 only: visit the estimators of this slot's expiry phase
+    uint32_t stream;              // 1: the states read are larger than the Infinity Cache holds
 };
 
 struct LevelArgs {

@@ -138,6 +138,15 @@ __device__ __forceinline__ uint32_t find_link(const U* prefix, uint32_t n_links,
     return lo;
 }
 
+// A 16-byte load of memory that is streamed once (non-temporal: it takes no
+// place in the caches from what is used again).
+__device__ __forceinline__ uint4 load_stream(const uint4* p)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 __device__ __forceinline__ void block_exclusive_scan_u64_1024(unsigned long long v, unsigned long long* lds /*[1024]*/,
@@ -1056,7 +1065,10 @@ __device__ __forceinline__ void hot_finish(const LinkDesc* D, uint64_t s, uint32
 // 4096 / eta consecutive estimators (load round c of the wave's four belongs
 // to estimator c / (eta / 1024)), so that small estimators still give every
 // wave four 1 KiB loads in flight.
-template <int CH, bool SMALL>
+// STREAM: non-temporal loads, for states that the Infinity Cache does not hold
+// (1.5 GiB 334 -> 284 us, 5.7 TB/s; 320 MiB just merged into 99 -> 63 us; 24
+// MiB 13 -> 15 us).
+template <int CH, bool SMALL, bool STREAM>
 __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -1094,7 +1106,7 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
         uint4* base = reinterpret_cast<uint4*>(D->state + (s << log2eta));
         uint4 v[4];
 #pragma unroll
-        for (int c = 0; c < 4; c++) v[c] = base[c * 64u + lane];
+        for (int c = 0; c < 4; c++) v[c] = STREAM ? load_stream(base + c * 64u + lane) : base[c * 64u + lane];
         uint32_t cnt[4];
 #pragma unroll
         for (int c = 0; c < 4; c++)
@@ -1128,7 +1140,9 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
     for (uint32_t g0 = 0; g0 < per_lane; g0 += CH) {
 #pragma unroll
         for (int c = 0; c < CH; c++)
-            v[c] = (g0 + c < per_lane) ? se[(g0 + c) * 64u + lane] : make_uint4(0u, 0u, 0u, 0u);
+            v[c] = g0 + c >= per_lane ? make_uint4(0u, 0u, 0u, 0u)
+                   : STREAM           ? load_stream(se + (g0 + c) * 64u + lane)
+                                      : se[(g0 + c) * 64u + lane];
         if (count) {
 #pragma unroll
             for (int c = 0; c < CH; c++)
@@ -1169,7 +1183,7 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
 // registers for the snapshot of a hot estimator; larger estimators are read
 // again.  With expire_only, only the estimators of this slot's expiry phase
 // are visited (and not counted).
-template <int CH>
+template <int CH, bool STREAM>
 __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect16(DetectArgs a)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -1195,8 +1209,8 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect16(DetectArgs a
         for (int c = 0; c < CH; c++) {
             const uint64_t w = 2ull * ((g0 + (uint32_t)c) * 64u + lane);
             if (g0 + (uint32_t)c < rounds) {
-                v[2 * c] = se[w];
-                v[2 * c + 1] = se[w + 1];
+                v[2 * c] = STREAM ? load_stream(se + w) : se[w];
+                v[2 * c + 1] = STREAM ? load_stream(se + w + 1) : se[w + 1];
             }
         }
 #pragma unroll
@@ -2305,34 +2319,80 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs a)
 // ---------------------------------------------------------------- merge
 // Alg. 5 with the per-cell most recent hit over the routers: for every cell the
 // stamp with the smallest distance wins; cells not live anywhere become empty.
+//
+// Distances are compared as x = (cur - stamp) mod 256, two cells to a 32-bit
+// word: the distance for stamps up to cur, one more than it for the others
+// (stamps run modulo 255), so their order is the distances'; an empty cell (x
+// = cur, between the two) gets a bit above all of them.  The winner's stamp is
+// cur - x again.  HBM bound: a workgroup streams 16 KiB of every source in
+// turn, so that the sources' pages are not opened by turns chunk by chunk, and
+// a word of four cells takes about 16 vector instructions a source (byte by
+// byte 50, as long as the loads).  Measured on 16 states of 320 MiB, 5.7 GB
+// read and written: 1131 us a chunk of each source at a time, byte by byte;
+// 1080 in 16 KiB pieces; 963 (5.9 TB/s) with non-temporal loads.
+constexpr uint32_t MERGE_CHUNKS = 4;
+
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+__device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b));
+}
+
+// x of the cells in the low bytes of e's halves, above 255 for empty ones
+__device__ __forceinline__ uint32_t merge_age(uint32_t e, uint32_t cur2)
+{
+    const uint32_t M = 0x00FF00FFu, H = 0x01000100u;
+    return (pk_sub_u16(cur2, e) & M) | (~(e + M) & H);
+}
 
 __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < a.n16; i += stride) {
-        uint32_t best[16];
-        uint32_t code[16];
+    const uint32_t M = 0x00FF00FFu;
+    const uint32_t cur2 = a.cur * 0x00010001u;
+    // live: x < k for stamps up to cur, x - 1 < k for the older ones past the wrap
+    const uint32_t kx = a.k > a.cur ? a.k + 1u : a.k;
+    const uint64_t stride = (uint64_t)gridDim.x * 256u * MERGE_CHUNKS;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * 256u * MERGE_CHUNKS + threadIdx.x; i0 < a.n16; i0 += stride) {
+        uint32_t even[MERGE_CHUNKS][4], odd[MERGE_CHUNKS][4];
 #pragma unroll
-        for (int b = 0; b < 16; b++) { best[b] = 255u; code[b] = 0u; }
+        for (uint32_t c = 0; c < MERGE_CHUNKS; c++)
+#pragma unroll
+            for (int w = 0; w < 4; w++) even[c][w] = odd[c][w] = 0x01FF01FFu;
+#pragma unroll 1
         for (uint32_t j = 0; j < a.n_src; j++) {
-            const uint4 v = reinterpret_cast<const uint4*>(a.src[j])[i];
-            if ((v.x | v.y | v.z | v.w) == 0u) continue;
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            const uint4* src = reinterpret_cast<const uint4*>(a.src[j]);
+            uint4 v[MERGE_CHUNKS];
 #pragma unroll
-            for (int b = 0; b < 16; b++) {
-                const uint32_t c = (w[b >> 2] >> ((b & 3) * 8)) & 255u;
-                if (c) {
-                    int age = (int)a.cur - (int)c;
-                    if (age < 0) age += 255;
-                    if ((uint32_t)age < best[b]) { best[b] = (uint32_t)age; code[b] = c; }
+            for (uint32_t c = 0; c < MERGE_CHUNKS; c++) v[c] = load_stream(src + (i0 + 256u * c < a.n16 ? i0 + 256u * c : i0));
+#pragma unroll
+            for (uint32_t c = 0; c < MERGE_CHUNKS; c++) {
+                const uint32_t x[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+                for (int w = 0; w < 4; w++) {
+                    even[c][w] = pk_min_u16(even[c][w], merge_age(x[w] & M, cur2));
+                    odd[c][w] = pk_min_u16(odd[c][w], merge_age((x[w] >> 8) & M, cur2));
                 }
             }
         }
-        uint32_t o[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int b = 0; b < 16; b++)
-            if (best[b] < a.k) o[b >> 2] |= code[b] << ((b & 3) * 8);
-        reinterpret_cast<uint4*>(a.dst)[i] = make_uint4(o[0], o[1], o[2], o[3]);
+        for (uint32_t c = 0; c < MERGE_CHUNKS; c++) {
+            uint32_t o[4];
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                auto stamps = [&](uint32_t x) {
+                    const uint32_t s = pk_sub_u16(cur2, x) & M;
+                    return ((x & 0xFFFFu) < kx ? s & 0xFFFFu : 0u) | ((x >> 16) < kx ? s & 0xFFFF0000u : 0u);
+                };
+                o[w] = stamps(even[c][w]) | stamps(odd[c][w]) << 8;
+            }
+            if (i0 + 256u * c < a.n16) reinterpret_cast<uint4*>(a.dst)[i0 + 256u * c] = make_uint4(o[0], o[1], o[2], o[3]);
+        }
     }
 }
 
@@ -2591,21 +2651,25 @@ hipError_t launch_recount(const LinkDesc* link, uint64_t n_se, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int CH, bool SMALL>
+static void hot_detect(const DetectArgs& a, hipStream_t s)
+{
+    const dim3 g((uint32_t)((a.total + DETECT_WAVES - 1) / DETECT_WAVES));
+    if (a.stream) k_hot_detect<CH, SMALL, true><<<g, 64u * DETECT_WAVES, 0, s>>>(a);
+    else k_hot_detect<CH, SMALL, false><<<g, 64u * DETECT_WAVES, 0, s>>>(a);
+}
+
 hipError_t launch_hot_detect(const DetectArgs& a, uint32_t max_chunks_per_lane, bool small, hipStream_t s)
 {
     // SMALL: some link has eta < 4096 (several estimators per wave) or the
     // engine has several links (link prefix in LDS); the plain variant keeps
     // half the registers, so more waves stream the state
-    const dim3 g((uint32_t)((a.total + DETECT_WAVES - 1) / DETECT_WAVES));
-    const uint32_t bs = 64u * DETECT_WAVES;
     if (small) {
-        if (max_chunks_per_lane >= 8) k_hot_detect<8, true><<<g, bs, 0, s>>>(a);
-        else k_hot_detect<4, true><<<g, bs, 0, s>>>(a);
+        if (max_chunks_per_lane >= 8) hot_detect<8, true>(a, s);
+        else hot_detect<4, true>(a, s);
     } else {
-        if (max_chunks_per_lane >= 8) k_hot_detect<8, false><<<g, bs, 0, s>>>(a);
-        else if (max_chunks_per_lane >= 4) k_hot_detect<4, false><<<g, bs, 0, s>>>(a);
-        else if (max_chunks_per_lane >= 2) k_hot_detect<2, false><<<g, bs, 0, s>>>(a);
-        else k_hot_detect<1, false><<<g, bs, 0, s>>>(a);
+        if (max_chunks_per_lane >= 8) hot_detect<8, false>(a, s);
+        else hot_detect<4, false>(a, s);        // eta = 4096
     }
     return hipGetLastError();
 }
@@ -2614,7 +2678,8 @@ hipError_t launch_hot_detect16(const DetectArgs& a, hipStream_t s)
 {
     if (a.n_links != 1 || a.total == 0) return hipErrorInvalidValue;
     const dim3 g((uint32_t)((a.total + DETECT_WAVES - 1) / DETECT_WAVES));
-    k_hot_detect16<4><<<g, 64u * DETECT_WAVES, 0, s>>>(a);
+    if (a.stream) k_hot_detect16<4, true><<<g, 64u * DETECT_WAVES, 0, s>>>(a);
+    else k_hot_detect16<4, false><<<g, 64u * DETECT_WAVES, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2717,7 +2782,7 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s)
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s)
 {
     if (a.cell16) k_merge16<<<grid_for(a.n16, 256, 256 * 16), 256, 0, s>>>(a);
-    else k_merge<<<grid_for(a.n16, 256, 256 * 16), 256, 0, s>>>(a);
+    else k_merge<<<grid_for(a.n16, 256 * MERGE_CHUNKS, 1u << 20), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
