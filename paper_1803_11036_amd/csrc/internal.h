@@ -231,19 +231,20 @@ inline uint32_t bin_lds_words(uint32_t n_bins, uint32_t pb, uint32_t r) { return
 // 144 KiB, which leave room for the overlapped close's workgroups, measured
 // the same)
 constexpr uint32_t BIN_LDS_WORDS = 40960u - 32u;
+constexpr uint32_t BIN_HALF_WORDS = 20480u - 32u;     // two workgroups a compute unit
 hipError_t launch_bin(const BinArgs& a, hipStream_t s);
 hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);
 hipError_t launch_apply_counted(const ApplyArgs& a, hipStream_t s);
 // Workgroups of one link in the multi-link launches (multiples of 8): its
-// binning, its uncounted stores and its counted stores.  The variant of the
-// binning kernel (0 general, else the register binning of that many rows).
+// binning, its uncounted stores and its counted stores.  Whether its binning
+// workgroups' LDS lets two share a compute unit.
 uint32_t bin_workgroups(const BinArgs& a);
 uint32_t apply_workgroups(const ApplyArgs& a);
 uint32_t apply_counted_workgroups(const ApplyArgs& a);
-uint32_t bin_variant(const BinArgs& a);
-// one launch over several links: bin (all of one variant), apply (uncounted,
+bool bin_half(const BinArgs& a);
+// one launch over several links: bin (all of bin_half `half`), apply (uncounted,
 // packed offsets, 8-bit cells), counted apply (lds_bytes: the largest need)
-hipError_t launch_bin_multi(const MultiBinArgs& m, uint32_t total_wg, hipStream_t s);
+hipError_t launch_bin_multi(const MultiBinArgs& m, uint32_t total_wg, bool half, hipStream_t s);
 hipError_t launch_apply_multi(const MultiApplyArgs& m, uint32_t total_wg, hipStream_t s);
 hipError_t launch_apply_counted_multi(const MultiApplyArgs& m, uint32_t total_wg, uint32_t lds_bytes, hipStream_t s);
 // bitmap stores of 16-bit cells (no counters): bins of 2^10 .. 2^MARKED16_MAX_SHIFT

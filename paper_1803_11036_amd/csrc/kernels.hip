@@ -18,6 +18,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <utility>
+
 #include "internal.h"
 
 namespace ssd {
@@ -428,13 +430,15 @@ __device__ __forceinline__ void pair_hashes(const uint32_t* tab, uint2 pr, uint3
     *h0 = tab_hash(tab, pr.x) & ((1u << q) - 1u);               // RHFG[0](cip)
 }
 
-__device__ __forceinline__ uint64_t cell_addr(uint2 pr, uint32_t i, uint32_t h0, uint32_t d, uint32_t q,
-                                              uint32_t delta, uint32_t log2eta)
+// Row i's estimator of a pair.  A bin holds whole estimators (2^(bin_shift -
+// log2eta) of them), so the bin and the offset in it come from the estimator's
+// number in 32 bits (with 64-bit cell addresses k_bin took 96.6 us on 6 M pairs
+// of six rows and now 94.8: the staging in LDS bounds it).
+__device__ __forceinline__ uint32_t estimator(uint2 pr, uint32_t i, uint32_t h0, uint32_t q, uint32_t delta)
 {
     const uint32_t col = i == 0 ? h0 : ((shr32(pr.x, (i - 1) * delta) ^ h0) & ((1u << q) - 1u));
-    return ((((uint64_t)i << q) | col) << log2eta) | d;
+    return (i << q) | col;
 }
-
 
 // The segment (chunk of pairs) of this binning workgroup: workgroup g runs on
 // XCD g mod 8, which takes a contiguous eighth of the segments, so that the
@@ -492,13 +496,13 @@ __device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32
     __syncthreads();
     const uint64_t p0 = (uint64_t)sg * a.pb;
     const uint32_t np = (uint32_t)min((uint64_t)a.pb, a.n - p0);
-    const uint32_t q = a.q, r = a.r, delta = a.delta, log2eta = a.log2eta, bs = a.bin_shift;
-    const uint32_t bmask = (1u << bs) - 1u;
+    const uint32_t q = a.q, r = a.r, delta = a.delta, log2eta = a.log2eta, es = a.bin_shift - log2eta;
+    const uint32_t emask = (1u << es) - 1u;
     for (uint32_t p = threadIdx.x; p < np; p += 1024u) {
         const uint2 pr = a.pairs[p0 + p];
         uint32_t h0, d;
         pair_hashes(tab, pr, q, log2eta, &h0, &d);
-        for (uint32_t i = 0; i < r; i++) atomicAdd(&hist[(uint32_t)(cell_addr(pr, i, h0, d, q, delta, log2eta) >> bs)], 1u);
+        for (uint32_t i = 0; i < r; i++) atomicAdd(&hist[estimator(pr, i, h0, q, delta) >> es], 1u);
     }
     __syncthreads();
     const uint32_t per = (a.n_bins + 1023u) / 1024u;
@@ -520,8 +524,8 @@ __device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32
         uint32_t h0, d;
         pair_hashes(tab, pr, q, log2eta, &h0, &d);
         for (uint32_t i = 0; i < r; i++) {
-            const uint64_t addr = cell_addr(pr, i, h0, d, q, delta, log2eta);
-            stage[atomicAdd(&hist[(uint32_t)(addr >> bs)], 1u)] = (uint32_t)addr & bmask;
+            const uint32_t se = estimator(pr, i, h0, q, delta);
+            stage[atomicAdd(&hist[se >> es], 1u)] = ((se & emask) << log2eta) | d;
         }
     }
     __syncthreads();
@@ -544,8 +548,8 @@ __device__ __forceinline__ void bin_reg(const BinArgs& a, uint32_t g, uint32_t* 
     __syncthreads();
     const uint64_t p0 = (uint64_t)sg * a.pb;
     const uint32_t np = (uint32_t)min((uint64_t)a.pb, a.n - p0);
-    const uint32_t q = a.q, delta = a.delta, log2eta = a.log2eta, bs = a.bin_shift;
-    const uint32_t bmask = (1u << bs) - 1u;
+    const uint32_t q = a.q, delta = a.delta, log2eta = a.log2eta, es = a.bin_shift - log2eta;
+    const uint32_t emask = (1u << es) - 1u;
     uint32_t off[PPT][R], key[PPT][R];
 #pragma unroll
     for (int u = 0; u < PPT; u++) {
@@ -556,9 +560,8 @@ __device__ __forceinline__ void bin_reg(const BinArgs& a, uint32_t g, uint32_t* 
         pair_hashes(tab, pr, q, log2eta, &h0, &d);
 #pragma unroll
         for (int i = 0; i < R; i++) {
-            const uint64_t addr = cell_addr(pr, i, h0, d, q, delta, log2eta);
-            const uint32_t bin = (uint32_t)(addr >> bs);
-            off[u][i] = (uint32_t)addr & bmask;
+            const uint32_t se = estimator(pr, i, h0, q, delta), bin = se >> es;
+            off[u][i] = ((se & emask) << log2eta) | d;
             key[u][i] = (bin << 16) | atomicAdd(&hist[bin], 1u);
         }
     }
@@ -587,9 +590,14 @@ __device__ __forceinline__ void bin_reg(const BinArgs& a, uint32_t g, uint32_t* 
     write_segment(a, sg, stage, np * R);
 }
 
-// R = 0: the general binning; else the register binning of R rows.
-template <int R, int PPT>
-__global__ __launch_bounds__(1024) void k_bin(BinArgs a)
+// R = 0: the general binning; else the register binning of R rows.  HALF: the
+// workgroup's LDS and registers are at most half a compute unit's, so that two
+// share it and one's loads and barriers overlap the other's LDS work: LDS
+// is active less than half of a full-size workgroup's time.  64 links' 23 M
+// pairs: 1246 us with whole segments, 1152 with halves where their runs are
+// long enough; 6 M pairs of five rows into 320 MiB of 16-bit cells 64 and 55.
+template <int R, int PPT, bool HALF>
+__global__ __launch_bounds__(1024, HALF ? 8 : 4) void k_bin(BinArgs a)
 {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t wsum[16];
@@ -602,16 +610,20 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs a)
 // workgroups, so that the dealing of its segments to XCDs is the one of a
 // launch of its own.  Each workgroup takes its link's binning variant (the
 // register binning of five or six rows where the segment fits it, else the
-// general one); the launch keeps the larger register count of the two.
-__global__ __launch_bounds__(1024) void k_bin_multi_rows(MultiBinArgs m)
+// general one); the launch keeps the larger register count of the two.  The
+// links whose segments leave room for two workgroups on a compute unit (HALF)
+// take a launch of their own.
+template <bool HALF>
+__global__ __launch_bounds__(1024, HALF ? 8 : 4) void k_bin_multi_rows(MultiBinArgs m)
 {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t wsum[16];
     const uint32_t l = uniform(find_link(m.wg_prefix, m.n, blockIdx.x));
     const BinArgs a = m.args[l];
     const uint32_t g = blockIdx.x - m.wg_prefix[l];
-    if (a.r == 6 && a.pb <= 6u * 1024u) bin_reg<6, 6>(a, g, lds, wsum);
-    else if (a.r == 5 && a.pb <= 7u * 1024u) bin_reg<5, 7>(a, g, lds, wsum);
+    constexpr int P6 = HALF ? 3 : 6, P5 = HALF ? 4 : 7;
+    if (a.r == 6 && a.pb <= P6 * 1024u) bin_reg<6, P6>(a, g, lds, wsum);
+    else if (a.r == 5 && a.pb <= P5 * 1024u) bin_reg<5, P5>(a, g, lds, wsum);
     else bin_generic(a, g, lds, wsum);
 }
 
@@ -2510,22 +2522,24 @@ static hipError_t bin_lds_attr()
 {
     static bool attr = false;
     if (attr) return hipSuccess;
-    for (const void* f : {reinterpret_cast<const void*>(&k_bin<0, 0>), reinterpret_cast<const void*>(&k_bin<6, 6>),
-                          reinterpret_cast<const void*>(&k_bin<5, 7>),
-                          reinterpret_cast<const void*>(&k_bin_multi_rows)}) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(BIN_LDS_WORDS * 4u));
+    const std::pair<const void*, uint32_t> kernels[] = {
+        {reinterpret_cast<const void*>(&k_bin<0, 0, false>), BIN_LDS_WORDS},
+        {reinterpret_cast<const void*>(&k_bin<6, 6, false>), BIN_LDS_WORDS},
+        {reinterpret_cast<const void*>(&k_bin<5, 7, false>), BIN_LDS_WORDS},
+        {reinterpret_cast<const void*>(&k_bin_multi_rows<false>), BIN_LDS_WORDS},
+        {reinterpret_cast<const void*>(&k_bin<0, 0, true>), BIN_HALF_WORDS},
+        {reinterpret_cast<const void*>(&k_bin<6, 3, true>), BIN_HALF_WORDS},
+        {reinterpret_cast<const void*>(&k_bin<5, 4, true>), BIN_HALF_WORDS},
+        {reinterpret_cast<const void*>(&k_bin_multi_rows<true>), BIN_HALF_WORDS}};
+    for (const auto& k : kernels) {
+        hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(k.second * 4u));
         if (e != hipSuccess) return e;
     }
     attr = true;
     return hipSuccess;
 }
 
-uint32_t bin_variant(const BinArgs& a)
-{
-    if (a.r == 6 && a.pb <= 6u * 1024u) return 6;
-    if (a.r == 5 && a.pb <= 7u * 1024u) return 5;
-    return 0;
-}
+bool bin_half(const BinArgs& a) { return bin_lds_words(a.n_bins, a.pb, a.r) <= BIN_HALF_WORDS; }
 
 uint32_t bin_workgroups(const BinArgs& a) { return 8u * ((a.blocks + 7u) / 8u); }   // segments dealt to XCDs in eighths
 
@@ -2535,21 +2549,27 @@ hipError_t launch_bin(const BinArgs& a, hipStream_t s)
     if (a.blocks == 0 || words > BIN_LDS_WORDS) return hipErrorInvalidValue;
     hipError_t e = bin_lds_attr();
     if (e != hipSuccess) return e;
-    const uint32_t grid = bin_workgroups(a);
-    switch (bin_variant(a)) {
-    case 6: k_bin<6, 6><<<grid, 1024, words * 4u, s>>>(a); break;
-    case 5: k_bin<5, 7><<<grid, 1024, words * 4u, s>>>(a); break;
-    default: k_bin<0, 0><<<grid, 1024, words * 4u, s>>>(a); break;
+    const uint32_t grid = bin_workgroups(a), lds = words * 4u;
+    if (bin_half(a)) {
+        if (a.r == 6 && a.pb <= 3u * 1024u) k_bin<6, 3, true><<<grid, 1024, lds, s>>>(a);
+        else if (a.r == 5 && a.pb <= 4u * 1024u) k_bin<5, 4, true><<<grid, 1024, lds, s>>>(a);
+        else k_bin<0, 0, true><<<grid, 1024, lds, s>>>(a);
+    } else {
+        if (a.r == 6 && a.pb <= 6u * 1024u) k_bin<6, 6, false><<<grid, 1024, lds, s>>>(a);
+        else if (a.r == 5 && a.pb <= 7u * 1024u) k_bin<5, 7, false><<<grid, 1024, lds, s>>>(a);
+        else k_bin<0, 0, false><<<grid, 1024, lds, s>>>(a);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_bin_multi(const MultiBinArgs& m, uint32_t total_wg, hipStream_t s)
+hipError_t launch_bin_multi(const MultiBinArgs& m, uint32_t total_wg, bool half, hipStream_t s)
 {
     if (m.n == 0 || total_wg == 0) return hipErrorInvalidValue;
     hipError_t e = bin_lds_attr();
     if (e != hipSuccess) return e;
-    k_bin_multi_rows<<<total_wg, 1024, BIN_LDS_WORDS * 4u, s>>>(m);    // every link's plan fits the LDS
+    // every link's plan fits the LDS
+    if (half) k_bin_multi_rows<true><<<total_wg, 1024, BIN_HALF_WORDS * 4u, s>>>(m);
+    else k_bin_multi_rows<false><<<total_wg, 1024, BIN_LDS_WORDS * 4u, s>>>(m);
     return hipGetLastError();
 }
 

@@ -295,8 +295,8 @@ struct Layout {
 
 // Arguments of a batch's multi-link binned launches for n links: per link
 // one BinArgs and one ApplyArgs, and the workgroup prefixes of the launches
-// (at most five per group of links -- three binning variants, counted and
-// uncounted stores -- and at most n groups: 10 (n + 1) words).
+// (at most five per group of links -- two of binning, three of stores -- and at
+// most n groups: 10 (n + 1) words).
 uint64_t multi_args_bytes(uint32_t n)
 {
     return align_up((uint64_t)n * sizeof(BinArgs)) + align_up((uint64_t)n * sizeof(ApplyArgs)) +
@@ -719,7 +719,15 @@ struct BinnedCall {
     BinPlan bp;
     uint64_t seg = 0;        // offsets per binning workgroup (pb * r)
 };
-BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_bytes)
+// Binning workgroups take half a compute unit (bin_half) where a bin's run in
+// their segments still has at least HALF_MIN_RUN offsets (48 bytes): shorter
+// runs cost the stores more than the binning gains.  2 M pairs of six rows
+// into 3072 bins (runs of 6): binning and stores 401 us with whole segments,
+// 409 with halves; 64 links' 23 M pairs: 5549 us with the line at 24, 5433 at
+// 12, 5448 at 4.  16 routers' slots of 1 to 4 M pairs: 2465 us with whole
+// segments, 2379 with halves.
+constexpr uint32_t HALF_MIN_RUN = 12;
+BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_bytes, bool halves = true)
 {
     BinnedCall c;
     c.csh = e->counting[l] ? counted_shift(e->p[l], e->bin_req[l] ? e->bin_req[l] : e->counted_bin_bytes) : 0;
@@ -731,6 +739,13 @@ BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_byt
         c.marked = mp.shift <= MARKED16_MAX_SHIFT && n * e->p[l].r >= e->counted_min_items * mp.n_bins;
     }
     c.bp = bin_plan(e->p[l], c.counted ? 1ull << c.csh : c.marked ? MARKED16_BIN_BYTES : bin_bytes);
+    const uint32_t r = e->p[l].r, fixed = 2048u + c.bp.n_bins + 1u;
+    if (halves && fixed < BIN_HALF_WORDS) {
+        uint32_t pb = (BIN_HALF_WORDS - fixed) / r;
+        if (r == 6) pb = std::min(pb, 3u * 1024u);
+        if (r == 5) pb = std::min(pb, 4u * 1024u);
+        if ((uint64_t)pb * r >= (uint64_t)HALF_MIN_RUN * c.bp.n_bins) c.bp.pb = std::min(c.bp.pb, pb);
+    }
     c.seg = (uint64_t)c.bp.pb * e->p[l].r;
     return c;
 }
@@ -770,7 +785,8 @@ BinBufs engine_bins(const Engine* e)
 }
 
 // Pairs per binning workgroup of a call of n pairs scanned in launches of its
-// own: a whole number of rounds over the compute units, of at least
+// own: a whole number of rounds over the compute units (two workgroups on each
+// where their LDS allows it), of at least
 // MIN_BIN_PAIRS pairs a workgroup, where the staging holds the plan (the
 // largest workgroups left 33 of 256 compute units at work on a 200K-pair call,
 // and a quarter of them in the second round of a 2M-pair one).
@@ -778,8 +794,9 @@ void bin_fill(BinnedCall& c, uint32_t r, uint64_t n, const BinBufs& bb)
 {
     constexpr uint64_t CUS = 256, MIN_BIN_PAIRS = 2048;
     const uint64_t most = (n + c.bp.pb - 1) / c.bp.pb;
-    const uint64_t rounds = (most + CUS - 1) / CUS;
-    const uint64_t blocks = std::max<uint64_t>(1, std::min(rounds * CUS, (n + MIN_BIN_PAIRS - 1) / MIN_BIN_PAIRS));
+    const uint64_t round = CUS * (bin_lds_words(c.bp.n_bins, c.bp.pb, r) <= BIN_HALF_WORDS ? 2u : 1u);
+    const uint64_t rounds = (most + round - 1) / round;
+    const uint64_t blocks = std::max<uint64_t>(1, std::min(rounds * round, (n + MIN_BIN_PAIRS - 1) / MIN_BIN_PAIRS));
     const uint64_t pb = (n + blocks - 1) / blocks;
     if (pb >= c.bp.pb || blocks * pb * r > bb.items_words || blocks * (c.bp.n_bins + 1) > bb.table_words) return;
     c.bp.pb = (uint32_t)pb;
@@ -1550,7 +1567,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
     ApplyArgs* ha = reinterpret_cast<ApplyArgs*>(host + app_region);
     uint32_t* hp = reinterpret_cast<uint32_t*>(host + pre_region);
     struct Launch {
-        uint32_t kind;        // 1: binning (every variant); 10, 12 counted stores (LDS for two workgroups
+        uint32_t kind;        // 1, 2: binning (a compute unit, half of one); 10, 12 counted stores (LDS for two workgroups
                               // per compute unit, more); 11 uncounted stores
         uint32_t first, count, pre, total_wg, lds;
     };
@@ -1585,15 +1602,18 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
             io += p.items;
             to += p.table;
         }
-        // binning: one launch, each workgroup in its link's variant
-        {
-            Launch L{1u, nb, 0, np_words, 0, 0};
+        // binning: one launch for the links whose workgroups take half a
+        // compute unit and one for the others, each workgroup in its link's variant
+        for (uint32_t kind : {1u, 2u}) {
+            Launch L{kind, nb, 0, np_words, 0, 0};
             for (const BinArgs& x : ba) {
+                if (bin_half(x) != (kind == 2u)) continue;
                 hb[nb++] = x;
                 hp[np_words + L.count] = L.total_wg;
                 L.count++;
                 L.total_wg += bin_workgroups(x);
             }
+            if (!L.count) continue;
             hp[np_words + L.count] = L.total_wg;
             np_words += L.count + 1;
             launches.push_back(L);
@@ -1633,7 +1653,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
                 phase_end(e, pm, 0, 1);
             } else {
                 MultiBinArgs m{db + L.first, dp + L.pre, L.count};
-                HIPCHK(e, launch_bin_multi(m, L.total_wg, e->stream));
+                HIPCHK(e, launch_bin_multi(m, L.total_wg, L.kind == 2u, e->stream));
                 phase_end(e, pm, PHASE_SCAN_BIN, 1);
             }
         }
@@ -1932,7 +1952,8 @@ int ssd_scan_slice_noalloc(ssd_detector* d, const uint32_t* pairs_dev, uint64_t 
         // the binning's staging in this device's static array, looked up at
         // ssd_init_detector; one step for the whole call
         uint8_t* base = noalloc_scratch(e->device);
-        const BinnedCall c = binned_call(e, 0, n, d->bin_bytes);
+        // (planned with the largest segments, whose table is the smallest)
+        const BinnedCall c = binned_call(e, 0, n, d->bin_bytes, false);
         const uint64_t blocks = (n + c.bp.pb - 1) / c.bp.pb;
         const uint64_t items = align_up(blocks * c.seg * 4), table = (uint64_t)(c.bp.n_bins + 1) * blocks * 4;
         // what the segments leave of the array is the table's (smaller binning workgroups need more of it)
@@ -2878,9 +2899,12 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         uint8_t* host = static_cast<uint8_t*>(g->mb_pinned[buf]);
         BinArgs* hb = reinterpret_cast<BinArgs*>(host);
         ApplyArgs* ha = reinterpret_cast<ApplyArgs*>(host + app_region);
-        uint32_t* hp = reinterpret_cast<uint32_t*>(host + pre_region);    // [binning prefix][a prefix per store kind]
-        // the round's members by store kind: a launch per kind, with its own
-        // workgroup prefix
+        uint32_t* hp = reinterpret_cast<uint32_t*>(host + pre_region);    // a workgroup prefix per launch
+        // the round's members by binning class and by store kind: a launch
+        // each, with its own workgroup prefix
+        struct Part { uint32_t kind, first, count, pre, total_wg, lds; };
+        std::vector<Part> parts;
+        uint32_t nb = 0, na = 0, np_words = 0;
         std::vector<std::pair<BinArgs, ApplyArgs>> args(cnt);
         for (uint32_t x = 0; x < cnt; x++) {
             Binned& b = bm[round[x]];
@@ -2895,29 +2919,25 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
             aa.parts = (aa.blocks + aa.per_part - 1) / aa.per_part;
             b.done += np;
         }
-        std::stable_sort(args.begin(), args.end(),
-                         [](const auto& x, const auto& y) { return store_kind(x.second) < store_kind(y.second); });
-        struct Stores { uint32_t kind, first, count, total_wg, lds; };
-        std::vector<Stores> stores;
-        uint32_t bin_wg = 0, np_words = cnt + 1;
-        for (uint32_t x = 0; x < cnt; x++) {
-            hb[x] = args[x].first;
-            ha[x] = args[x].second;
-            hp[x] = bin_wg;
-            bin_wg += bin_workgroups(hb[x]);
-            const uint32_t kd = store_kind(ha[x]);
-            if (stores.empty() || stores.back().kind != kd) {
-                if (!stores.empty()) hp[np_words++] = stores.back().total_wg;
-                stores.push_back({kd, x, 0, 0, 0});
+        for (uint32_t kind : {1u, 2u, 10u, 12u, 11u}) {
+            Part P{kind, kind <= 2u ? nb : na, 0, np_words, 0, 0};
+            for (const auto& x : args) {
+                if (kind <= 2u ? bin_half(x.first) != (kind == 2u) : store_kind(x.second) != kind) continue;
+                hp[np_words + P.count++] = P.total_wg;
+                if (kind <= 2u) {
+                    hb[nb++] = x.first;
+                    P.total_wg += bin_workgroups(x.first);
+                } else {
+                    ha[na++] = x.second;
+                    P.total_wg += store_workgroups(x.second);
+                    P.lds = std::max(P.lds, store_lds(x.second));
+                }
             }
-            Stores& st = stores.back();
-            hp[np_words++] = st.total_wg;
-            st.count++;
-            st.total_wg += store_workgroups(ha[x]);
-            st.lds = std::max(st.lds, store_lds(ha[x]));
+            if (!P.count) continue;
+            hp[np_words + P.count] = P.total_wg;
+            np_words += P.count + 1;
+            parts.push_back(P);
         }
-        hp[cnt] = bin_wg;
-        hp[np_words++] = stores.back().total_wg;
         HIPCHK(e, hipMemcpyAsync(dev, host, multi_args_bytes(g->max_members), hipMemcpyHostToDevice, e->stream));
         HIPCHK(e, hipEventRecord(g->mb_done[buf], e->stream));
         g->mb_used[buf] = true;
@@ -2925,14 +2945,17 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
         // each member's own phase timing counts the launches that scanned it
         pm.resize(cnt);
         for (uint32_t x = 0; x < cnt; x++) pm[x] = phase_begin(&bm[round[x]].m->e);
-        HIPCHK(e, launch_bin_multi(MultiBinArgs{reinterpret_cast<const BinArgs*>(dev), dp, cnt}, bin_wg, e->stream));
+        for (const Part& P : parts) {
+            if (P.kind > 2u) continue;
+            const MultiBinArgs mb{reinterpret_cast<const BinArgs*>(dev) + P.first, dp + P.pre, P.count};
+            HIPCHK(e, launch_bin_multi(mb, P.total_wg, P.kind == 2u, e->stream));
+        }
         for (uint32_t x = 0; x < cnt; x++) phase_end(&bm[round[x]].m->e, pm[x], PHASE_SCAN_BIN, 1);
         for (uint32_t x = 0; x < cnt; x++) pm[x] = phase_begin(&bm[round[x]].m->e);
-        uint32_t pre_at = cnt + 1;
-        for (const Stores& st : stores) {
-            const MultiApplyArgs ma{reinterpret_cast<const ApplyArgs*>(dev + app_region) + st.first, dp + pre_at, st.count};
-            HIPCHK(e, launch_stores(ma, st.kind, st.total_wg, st.lds, e->stream));
-            pre_at += st.count + 1;
+        for (const Part& P : parts) {
+            if (P.kind <= 2u) continue;
+            const MultiApplyArgs ma{reinterpret_cast<const ApplyArgs*>(dev + app_region) + P.first, dp + P.pre, P.count};
+            HIPCHK(e, launch_stores(ma, P.kind, P.total_wg, P.lds, e->stream));
         }
         for (uint32_t x = 0; x < cnt; x++) phase_end(&bm[round[x]].m->e, pm[x], 0, 1);
     }
