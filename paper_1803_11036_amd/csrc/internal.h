@@ -125,7 +125,8 @@ struct BinArgs {
     uint32_t* table;              // [n_bins + 1][blocks] start of bin b in segment j; row n_bins = item count
     uint32_t q, r, delta, log2eta;
     uint32_t bin_shift, n_bins, pb, blocks;
-    uint32_t pack, pad;           // 1: three 21-bit offsets per 8-byte word (bins of at most 2 MiB)
+    uint32_t pack;                // 1: three 21-bit offsets per 8-byte word (bins of at most 2 MiB)
+    uint32_t rounds;              // segments per workgroup, one after another
 };
 
 // binned scan, step 2: the stores of every bin
@@ -231,6 +232,11 @@ inline uint32_t bin_lds_words(uint32_t n_bins, uint32_t pb, uint32_t r) { return
 // 144 KiB, which leave room for the overlapped close's workgroups, measured
 // the same)
 constexpr uint32_t BIN_LDS_WORDS = 40960u - 32u;
+constexpr uint32_t BIN_CUS = 256u;
+// Segments of a whole-size workgroup in a multi-link launch (64 links, 12
+// streams: 390 and 93 us at 2, 389 and 113 at 4, 415 and 112 at 8); a launch
+// of its own gives every compute unit one workgroup.
+constexpr uint32_t BIN_MULTI_ROUNDS = 2u;
 constexpr uint32_t BIN_HALF_WORDS = 20480u - 32u;     // two workgroups a compute unit
 hipError_t launch_bin(const BinArgs& a, hipStream_t s);
 hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);

@@ -167,6 +167,17 @@ __device__ __forceinline__ void block_exclusive_scan_u64_1024(unsigned long long
     __syncthreads();
 }
 
+// Workgroup barrier that orders LDS only: global stores issued before it stay
+// in flight (a plain __syncthreads waits for their completion).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// LOCAL: only LDS is ordered by its barriers.
+template <bool LOCAL = false>
 __device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t* lds /*[16]*/, uint32_t* total)
 {
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
@@ -177,14 +188,16 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32
         if (lane >= (uint32_t)o) incl += t;
     }
     if (lane == 63) lds[wid] = incl;
-    __syncthreads();
+    if (LOCAL) lds_barrier();
+    else __syncthreads();
     uint32_t off = 0, tot = 0;
     for (uint32_t w = 0; w < 16; w++) {
         uint32_t x = lds[w];
         off += w < wid ? x : 0u;
         tot += x;
     }
-    __syncthreads();
+    if (LOCAL) lds_barrier();
+    else __syncthreads();
     *total = tot;
     return off + incl - v;
 }
@@ -432,21 +445,25 @@ __device__ __forceinline__ void pair_hashes(const uint32_t* tab, uint2 pr, uint3
 
 // Row i's estimator of a pair.  A bin holds whole estimators (2^(bin_shift -
 // log2eta) of them), so the bin and the offset in it come from the estimator's
-// number in 32 bits (with 64-bit cell addresses k_bin took 96.6 us on 6 M pairs
-// of six rows and now 94.8: the staging in LDS bounds it).
-__device__ __forceinline__ uint32_t estimator(uint2 pr, uint32_t i, uint32_t h0, uint32_t q, uint32_t delta)
+// number in 32 bits (64-bit cell addresses cost k_bin 2 %).
+__device__ __forceinline__ uint32_t estimator(uint32_t x, uint32_t i, uint32_t h0, uint32_t q, uint32_t delta)
 {
-    const uint32_t col = i == 0 ? h0 : ((shr32(pr.x, (i - 1) * delta) ^ h0) & ((1u << q) - 1u));
+    const uint32_t col = i == 0 ? h0 : ((shr32(x, (i - 1) * delta) ^ h0) & ((1u << q) - 1u));
     return (i << q) | col;
 }
 
-// The segment (chunk of pairs) of this binning workgroup: workgroup g runs on
+// The segments (chunks of pairs) of a binning workgroup: workgroup g runs on
 // XCD g mod 8, which takes a contiguous eighth of the segments, so that the
 // bin table entries of neighbouring segments, which share sectors, are
-// written through one L2 and leave it merged.  At least the segment count.
-__device__ __forceinline__ uint32_t bin_segment(uint32_t g, uint32_t blocks)
+// written through one L2 and leave it merged; the XCD's workgroups take its
+// segments in turn, a.rounds each at most.
+struct BinSegments {
+    uint32_t at, end, step;
+};
+__device__ __forceinline__ BinSegments bin_segments(const BinArgs& a, uint32_t g)
 {
-    return (g & 7u) * ((blocks + 7u) >> 3) + (g >> 3);
+    const uint32_t per = (a.blocks + 7u) >> 3, first = (g & 7u) * per;
+    return {first + (g >> 3), min(first + per, a.blocks), (per + a.rounds - 1u) / a.rounds};
 }
 
 // A workgroup's sorted offsets out to its segment, coalesced: 4 bytes each, or
@@ -484,10 +501,8 @@ __device__ __forceinline__ uint32_t read_item(const ApplyArgs& a, uint32_t j, ui
 // k_apply's reads of the runs are dense.  Pass 1 counts the bins' offsets,
 // pass 2 hashes again and places each offset at its bin's next free slot.
 // (workgroup g of this link's launch; lds: the dynamic LDS, wsum: 16 words)
-__device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32_t* lds, uint32_t* wsum)
+__device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t sg, uint32_t* lds, uint32_t* wsum)
 {
-    const uint32_t sg = bin_segment(g, a.blocks);
-    if (sg >= a.blocks) return;
     uint32_t* tab = lds;
     uint32_t* hist = lds + 2048;
     uint32_t* stage = hist + a.n_bins + 1;
@@ -502,7 +517,7 @@ __device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32
         const uint2 pr = a.pairs[p0 + p];
         uint32_t h0, d;
         pair_hashes(tab, pr, q, log2eta, &h0, &d);
-        for (uint32_t i = 0; i < r; i++) atomicAdd(&hist[estimator(pr, i, h0, q, delta) >> es], 1u);
+        for (uint32_t i = 0; i < r; i++) atomicAdd(&hist[estimator(pr.x, i, h0, q, delta) >> es], 1u);
     }
     __syncthreads();
     const uint32_t per = (a.n_bins + 1023u) / 1024u;
@@ -524,7 +539,7 @@ __device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32
         uint32_t h0, d;
         pair_hashes(tab, pr, q, log2eta, &h0, &d);
         for (uint32_t i = 0; i < r; i++) {
-            const uint32_t se = estimator(pr, i, h0, q, delta);
+            const uint32_t se = estimator(pr.x, i, h0, q, delta);
             stage[atomicAdd(&hist[se >> es], 1u)] = ((se & emask) << log2eta) | d;
         }
     }
@@ -532,62 +547,98 @@ __device__ __forceinline__ void bin_generic(const BinArgs& a, uint32_t g, uint32
     write_segment(a, sg, stage, np * r);
 }
 
-// The same sort for the common row counts with every item kept in registers
-// between the two passes (R rows, up to PPT pairs per thread): the pairs are
-// hashed once, and each offset's rank in its bin comes from the count pass.
-template <int R, int PPT>
+// Segment sg's pairs, PPT per thread (past the end: the last pair).
+template <int PPT>
+__device__ __forceinline__ void load_pairs(const BinArgs& a, uint32_t sg, uint2* pr)
+{
+    const uint64_t p0 = (uint64_t)sg * a.pb;
+    const uint32_t np = (uint32_t)min((uint64_t)a.pb, a.n - p0);
+#pragma unroll
+    for (int u = 0; u < PPT; u++) pr[u] = a.pairs[p0 + min(threadIdx.x + u * 1024u, np - 1u)];
+}
+
+// The same sort for the common row counts (R rows, up to PPT pairs per thread)
+// with the hashes of every pair and each offset's rank in its bin (of the
+// count pass) kept in registers between the two passes; bins and offsets are
+// cheap to form again, and kept instead they left no registers to load ahead.
+// PIPE: a workgroup sorts its segments one after another, and the pairs of
+// the next are loaded while this one is placed and written; no barrier waits
+// for them or for the segment's stores.  (6 M pairs of six rows: 97 us with a
+// workgroup per segment, 69 so: the loads were 29 of them.  The phases now
+// follow one another in every compute unit: hashing, the counts in LDS, the
+// scan with the table's stores, the placing and the writing take about a
+// fifth each.  Workgroups of half a compute unit overlap each other's loads
+// and take one segment: 2.7 M pairs of five rows 26.5 us, in turn 28.)
+template <int R, int PPT, bool PIPE>
 __device__ __forceinline__ void bin_reg(const BinArgs& a, uint32_t g, uint32_t* lds, uint32_t* wsum)
 {
-    const uint32_t sg = bin_segment(g, a.blocks);
-    if (sg >= a.blocks) return;
+    const BinSegments S = bin_segments(a, g);
+    if (S.at >= S.end) return;
     uint32_t* tab = lds;
     uint32_t* hist = lds + 2048;
     uint32_t* stage = hist + a.n_bins + 1;
+    uint2 pr[PPT];
+    load_pairs<PPT>(a, S.at, pr);
     for (uint32_t i = threadIdx.x; i < 2048u; i += 1024u) tab[i] = a.tables[i];
-    for (uint32_t i = threadIdx.x; i <= a.n_bins; i += 1024u) hist[i] = 0u;
-    __syncthreads();
-    const uint64_t p0 = (uint64_t)sg * a.pb;
-    const uint32_t np = (uint32_t)min((uint64_t)a.pb, a.n - p0);
     const uint32_t q = a.q, delta = a.delta, log2eta = a.log2eta, es = a.bin_shift - log2eta;
     const uint32_t emask = (1u << es) - 1u;
-    uint32_t off[PPT][R], key[PPT][R];
-#pragma unroll
-    for (int u = 0; u < PPT; u++) {
-        const uint32_t p = threadIdx.x + u * 1024u;
-        if (p >= np) continue;
-        const uint2 pr = a.pairs[p0 + p];
-        uint32_t h0, d;
-        pair_hashes(tab, pr, q, log2eta, &h0, &d);
-#pragma unroll
-        for (int i = 0; i < R; i++) {
-            const uint32_t se = estimator(pr, i, h0, q, delta), bin = se >> es;
-            off[u][i] = ((se & emask) << log2eta) | d;
-            key[u][i] = (bin << 16) | atomicAdd(&hist[bin], 1u);
-        }
-    }
-    __syncthreads();
     const uint32_t per = (a.n_bins + 1023u) / 1024u;
     const uint32_t b0 = min(a.n_bins, threadIdx.x * per), b1 = min(a.n_bins, b0 + per);
-    uint32_t sum = 0;
-    for (uint32_t b = b0; b < b1; b++) sum += hist[b];
-    uint32_t total;
-    uint32_t start = block_exclusive_scan_1024(sum, wsum, &total);
-    for (uint32_t b = b0; b < b1; b++) {
-        const uint32_t c = hist[b];
-        hist[b] = start;
-        a.table[(uint64_t)b * a.blocks + sg] = start;
-        start += c;
-    }
-    if (threadIdx.x == 0) a.table[(uint64_t)a.n_bins * a.blocks + sg] = np * R;
-    __syncthreads();
+    for (uint32_t sg = S.at; sg < S.end; sg += S.step) {
+        const uint32_t np = (uint32_t)min((uint64_t)a.pb, a.n - (uint64_t)sg * a.pb);
+        for (uint32_t i = threadIdx.x; i <= a.n_bins; i += 1024u) hist[i] = 0u;
+        lds_barrier();               // (also: the segment before has left the staging)
+        uint32_t x[PPT], h0[PPT], d[PPT], rank[PPT][(R + 1) / 2];
 #pragma unroll
-    for (int u = 0; u < PPT; u++) {
-        if (threadIdx.x + u * 1024u >= np) continue;
+        for (int u = 0; u < PPT; u++) {
+            if (threadIdx.x + u * 1024u >= np) continue;
+            x[u] = pr[u].x;
+            pair_hashes(tab, pr[u], q, log2eta, &h0[u], &d[u]);
 #pragma unroll
-        for (int i = 0; i < R; i++) stage[hist[key[u][i] >> 16] + (key[u][i] & 0xFFFFu)] = off[u][i];
+            for (int i = 0; i < R; i++) {
+                const uint32_t at = atomicAdd(&hist[estimator(x[u], i, h0[u], q, delta) >> es], 1u);
+                if (i & 1) rank[u][i / 2] |= at << 16;
+                else rank[u][i / 2] = at;
+            }
+        }
+        if (PIPE && sg + S.step < S.end) load_pairs<PPT>(a, sg + S.step, pr);
+        lds_barrier();
+        uint32_t sum = 0;
+        for (uint32_t b = b0; b < b1; b++) sum += hist[b];
+        uint32_t total;
+        uint32_t start = block_exclusive_scan_1024<true>(sum, wsum, &total);
+        for (uint32_t b = b0; b < b1; b++) {
+            const uint32_t c = hist[b];
+            hist[b] = start;
+            a.table[(uint64_t)b * a.blocks + sg] = start;
+            start += c;
+        }
+        if (threadIdx.x == 0) a.table[(uint64_t)a.n_bins * a.blocks + sg] = np * R;
+        lds_barrier();
+#pragma unroll
+        for (int u = 0; u < PPT; u++) {
+            if (threadIdx.x + u * 1024u >= np) continue;
+#pragma unroll
+            for (int i = 0; i < R; i++) {
+                const uint32_t se = estimator(x[u], i, h0[u], q, delta);
+                const uint32_t at = (i & 1) ? rank[u][i / 2] >> 16 : rank[u][i / 2] & 0xFFFFu;
+                stage[hist[se >> es] + at] = ((se & emask) << log2eta) | d[u];
+            }
+        }
+        lds_barrier();
+        write_segment(a, sg, stage, np * R);
+        if (!PIPE) return;
     }
-    __syncthreads();
-    write_segment(a, sg, stage, np * R);
+}
+
+// The general binning of a workgroup's segments.
+__device__ __forceinline__ void bin_any(const BinArgs& a, uint32_t g, uint32_t* lds, uint32_t* wsum)
+{
+    const BinSegments S = bin_segments(a, g);
+    for (uint32_t sg = S.at; sg < S.end; sg += S.step) {
+        bin_generic(a, sg, lds, wsum);
+        __syncthreads();
+    }
 }
 
 // R = 0: the general binning; else the register binning of R rows.  HALF: the
@@ -595,14 +646,15 @@ __device__ __forceinline__ void bin_reg(const BinArgs& a, uint32_t g, uint32_t* 
 // share it and one's loads and barriers overlap the other's LDS work: LDS
 // is active less than half of a full-size workgroup's time.  64 links' 23 M
 // pairs: 1246 us with whole segments, 1152 with halves where their runs are
-// long enough; 6 M pairs of five rows into 320 MiB of 16-bit cells 64 and 55.
+// long enough (1020 with the register sort as it is now); 6 M pairs of five
+// rows into 320 MiB of 16-bit cells 64 and 55 (52).
 template <int R, int PPT, bool HALF>
 __global__ __launch_bounds__(1024, HALF ? 8 : 4) void k_bin(BinArgs a)
 {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t wsum[16];
-    if constexpr (R == 0) bin_generic(a, blockIdx.x, lds, wsum);
-    else bin_reg<R, PPT>(a, blockIdx.x, lds, wsum);
+    if constexpr (R == 0) bin_any(a, blockIdx.x, lds, wsum);
+    else bin_reg<R, PPT, !HALF>(a, blockIdx.x, lds, wsum);
 }
 
 // Several links in one launch: workgroup g belongs to the link whose range
@@ -622,9 +674,9 @@ __global__ __launch_bounds__(1024, HALF ? 8 : 4) void k_bin_multi_rows(MultiBinA
     const BinArgs a = m.args[l];
     const uint32_t g = blockIdx.x - m.wg_prefix[l];
     constexpr int P6 = HALF ? 3 : 6, P5 = HALF ? 4 : 7;
-    if (a.r == 6 && a.pb <= P6 * 1024u) bin_reg<6, P6>(a, g, lds, wsum);
-    else if (a.r == 5 && a.pb <= P5 * 1024u) bin_reg<5, P5>(a, g, lds, wsum);
-    else bin_generic(a, g, lds, wsum);
+    if (a.r == 6 && a.pb <= P6 * 1024u) bin_reg<6, P6, !HALF>(a, g, lds, wsum);
+    else if (a.r == 5 && a.pb <= P5 * 1024u) bin_reg<5, P5, !HALF>(a, g, lds, wsum);
+    else bin_any(a, g, lds, wsum);
 }
 
 // One wave per workgroup.  Workgroup g: XCD g mod 8, the (g mod 8) + 8 * (w /
@@ -765,15 +817,6 @@ __device__ __forceinline__ uint32_t stamp_word(uint32_t x, uint32_t m, uint32_t 
         if (d < k) cnt_add(cw, ce0 + (slot >= d ? slot - d : slot + k - d), -1);
     }
     return (x & ~chg) | ((stamp * 0x01010101u) & chg);
-}
-
-// Workgroup barrier that orders LDS only: global stores issued before it stay
-// in flight (a plain __syncthreads waits for their completion).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // The first half of the bitmap stores (bin `bin` of this launch): the LDS is
@@ -2541,12 +2584,15 @@ static hipError_t bin_lds_attr()
 
 bool bin_half(const BinArgs& a) { return bin_lds_words(a.n_bins, a.pb, a.r) <= BIN_HALF_WORDS; }
 
-uint32_t bin_workgroups(const BinArgs& a) { return 8u * ((a.blocks + 7u) / 8u); }   // segments dealt to XCDs in eighths
+uint32_t bin_workgroups(const BinArgs& a)      // segments dealt to XCDs in eighths
+{
+    return 8u * (((a.blocks + 7u) / 8u + a.rounds - 1u) / a.rounds);
+}
 
 hipError_t launch_bin(const BinArgs& a, hipStream_t s)
 {
     const uint32_t words = bin_lds_words(a.n_bins, a.pb, a.r);
-    if (a.blocks == 0 || words > BIN_LDS_WORDS) return hipErrorInvalidValue;
+    if (a.blocks == 0 || a.rounds == 0 || words > BIN_LDS_WORDS) return hipErrorInvalidValue;
     hipError_t e = bin_lds_attr();
     if (e != hipSuccess) return e;
     const uint32_t grid = bin_workgroups(a), lds = words * 4u;

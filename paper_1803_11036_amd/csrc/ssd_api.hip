@@ -792,9 +792,9 @@ BinBufs engine_bins(const Engine* e)
 // and a quarter of them in the second round of a 2M-pair one).
 void bin_fill(BinnedCall& c, uint32_t r, uint64_t n, const BinBufs& bb)
 {
-    constexpr uint64_t CUS = 256, MIN_BIN_PAIRS = 2048;
+    constexpr uint64_t MIN_BIN_PAIRS = 2048;
     const uint64_t most = (n + c.bp.pb - 1) / c.bp.pb;
-    const uint64_t round = CUS * (bin_lds_words(c.bp.n_bins, c.bp.pb, r) <= BIN_HALF_WORDS ? 2u : 1u);
+    const uint64_t round = BIN_CUS * (bin_lds_words(c.bp.n_bins, c.bp.pb, r) <= BIN_HALF_WORDS ? 2u : 1u);
     const uint64_t rounds = (most + round - 1) / round;
     const uint64_t blocks = std::max<uint64_t>(1, std::min(rounds * round, (n + MIN_BIN_PAIRS - 1) / MIN_BIN_PAIRS));
     const uint64_t pb = (n + blocks - 1) / blocks;
@@ -882,6 +882,7 @@ int enqueue_binned_scan(Engine* e, uint32_t l, const uint2* pairs, uint64_t n, u
         ba.pairs = pairs + done;
         ba.n = m;
         ba.blocks = (uint32_t)((m + bp.pb - 1) / bp.pb);
+        ba.rounds = bin_half(ba) ? 1u : (ba.blocks + BIN_CUS - 1u) / BIN_CUS;
         aa.blocks = ba.blocks;
         aa.parts = (ba.blocks + aa.per_part - 1) / aa.per_part;
         PhaseMark pm = phase_begin(e);
@@ -1597,6 +1598,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
             x.pairs = pairs + offsets[p.l];
             x.n = offsets[p.l + 1] - offsets[p.l];
             x.blocks = (uint32_t)p.blocks;
+            x.rounds = bin_half(x) ? 1u : BIN_MULTI_ROUNDS;
             y.blocks = x.blocks;
             y.parts = (y.blocks + y.per_part - 1) / y.per_part;
             io += p.items;
@@ -2915,6 +2917,7 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
             ba.pairs = reinterpret_cast<const uint2*>(pairs_dev) + b.begin + b.done;
             ba.n = np;
             ba.blocks = (uint32_t)((np + b.c.bp.pb - 1) / b.c.bp.pb);
+            ba.rounds = bin_half(ba) ? 1u : BIN_MULTI_ROUNDS;
             aa.blocks = ba.blocks;
             aa.parts = (aa.blocks + aa.per_part - 1) / aa.per_part;
             b.done += np;

@@ -43,3 +43,24 @@ def test_segments_against_oracle(q, r, delta, eta, cell_bits, bin_bytes):
             ssd.close_slice(g, advance_only=True)
             o.close(advance_only=True)
     g.destroy()
+
+
+@pytest.mark.parametrize("q,r,delta,full", [(16, 6, 4, 6144), (16, 5, 6, 7168), (16, 9, 3, 4063)])
+def test_several_segments_a_workgroup(q, r, delta, full):
+    """Calls of more whole segments than compute units, the last one ragged: workgroups take two or three in turn."""
+    g, o = make_pair(q, r, delta, 1024, 2, 60, tg.hash_tables(r), rehash=True, max_tuples=1 << 22)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SCAN_MODE, ssd.SSD_SCAN_BINNED)
+    ssd.set_tuning(g, ssd.SSD_TUNE_COUNTED, 0)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SCAN_BIN_BYTES, 1 << 18)
+    rng = np.random.default_rng(r)
+    hosts = rng.integers(0, 1 << 32, 1 << 16, dtype=np.uint32)
+    for t, n in enumerate([256 * full + 1, 512 * full + 1023]):
+        log(f"rounds q={q} r={r} n={n}")
+        p = np.empty((n, 2), dtype=np.uint32)
+        p[:, 0] = rng.choice(hosts, n)
+        p[:, 1] = rng.integers(0, 1 << 32, n, dtype=np.uint32)
+        scan_both(g, o, p, t)
+        compare_state(g, o)
+        ssd.close_slice(g, advance_only=True)
+        o.close(advance_only=True)
+    g.destroy()
