@@ -828,11 +828,14 @@ __device__ __forceinline__ uint32_t stamp_word(uint32_t x, uint32_t m, uint32_t 
 __device__ __forceinline__ void mark_runs(const ApplyArgs& a, uint32_t bin, uint32_t* lds, uint32_t bm_words,
                                           uint32_t n_words, uint16_t* list, uint32_t& n_list)
 {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const uint32_t* row = a.table + (uint64_t)bin * a.blocks;
-    // this lane's run (segment j) of the wave's first group, loaded before the
-    // LDS is cleared so that the two overlap
-    uint32_t j = wave * 64u + lane, st = 0, c = 0;
+    // a run is shared by 2^ls lanes where there are fewer runs than threads
+    // (64 links of 1 to 1024 runs a bin: 4275 us with a lane each, 4124 so)
+    const uint32_t ls = a.blocks * 2u <= blockDim.x ? 31u - (uint32_t)__clz(blockDim.x / a.blocks) : 0u;
+    const uint32_t part = threadIdx.x & ((1u << ls) - 1u);
+    // this lane's first run (segment j), loaded before the LDS is cleared so
+    // that the two overlap
+    uint32_t j = threadIdx.x >> ls, st = 0, c = 0;
     if (j < a.blocks) {
         st = row[j];
         c = row[a.blocks + j] - st;
@@ -840,26 +843,17 @@ __device__ __forceinline__ void mark_runs(const ApplyArgs& a, uint32_t bin, uint
     for (uint32_t i = threadIdx.x; i < n_words; i += blockDim.x) lds[i] = i < bm_words ? 0u : 0x80008000u;
     if (threadIdx.x == 0) n_list = 0u;
     __syncthreads();
-    // walk: lane j reads run j itself, four aligned 16-byte loads (24 offsets)
-    // at a time; words past the segment's end are read from its last pair and
-    // fall outside the run
+    // walk: four aligned 16-byte loads (24 offsets) of the run at a time;
+    // words past the segment's end are read from its last pair and fall
+    // outside the run
     const uint64_t seg_words = packed_seg_words(a.seg);
     const uint64_t* items = reinterpret_cast<const uint64_t*>(a.items);
     const uint32_t last_pair = (uint32_t)(seg_words / 2u) - 1u;
-    for (uint32_t jb = wave * 64u; jb < a.blocks; jb += 64u * CAPPLY_WAVES) {
-        if (jb != wave * 64u) {
-            j = jb + lane;
-            st = 0;
-            c = 0;
-            if (j < a.blocks) {
-                st = row[j];
-                c = row[a.blocks + j] - st;
-            }
-        }
+    for (;;) {
         const uint32_t end = st + c;                                   // items [st, end)
         const uint32_t w_end = (end + 2u) / 3u;
         const uint4* seg = reinterpret_cast<const uint4*>(items + (uint64_t)min(j, a.blocks - 1u) * seg_words);
-        for (uint32_t base = (st / 3u) & ~1u; c && base < w_end; base += 8u) {
+        for (uint32_t base = ((st / 3u) & ~1u) + 8u * part; c && base < w_end; base += 8u << ls) {
             uint4 q[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) q[i] = seg[min(base / 2u + (uint32_t)i, last_pair)];
@@ -879,6 +873,10 @@ __device__ __forceinline__ void mark_runs(const ApplyArgs& a, uint32_t bin, uint
                 }
             }
         }
+        j += blockDim.x >> ls;
+        if (j >= a.blocks) break;
+        st = row[j];
+        c = row[a.blocks + j] - st;
     }
     __syncthreads();
 }

@@ -64,3 +64,26 @@ def test_several_segments_a_workgroup(q, r, delta, full):
         ssd.close_slice(g, advance_only=True)
         o.close(advance_only=True)
     g.destroy()
+
+
+@pytest.mark.parametrize("cell_bits", [8, 16])
+def test_runs_shared_by_lanes(cell_bits):
+    """The bitmap stores with 1, 2, 3, 511, 512 and 513 runs a bin: shared by 1024 lanes down to one, empty runs and
+    runs of thousands of offsets, counters exact."""
+    g, o = make_pair(14, 6, 5, 1024, 3, 60, tg.hash_tables(3), rehash=True, cell_bits=cell_bits, max_tuples=1 << 22)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SCAN_MODE, ssd.SSD_SCAN_BINNED)
+    ssd.set_tuning(g, ssd.SSD_TUNE_COUNTED_MIN_ITEMS, 1)
+    rng = np.random.default_rng(1)
+    hosts, heavy = rng.integers(0, 1 << 32, 3000, dtype=np.uint32), rng.integers(0, 1 << 32, 6, dtype=np.uint32)
+    for t, runs in enumerate([1, 2, 3, 511, 512, 513]):
+        n = 2048 * runs - 5
+        log(f"shared runs bits={cell_bits} runs={runs}")
+        p = np.empty((n, 2), dtype=np.uint32)
+        p[:, 0] = rng.choice(hosts, n)
+        p[:, 1] = rng.integers(0, 40, n)
+        p[: n // 8, 0] = rng.choice(heavy, n // 8)
+        p[: n // 8, 1] = rng.integers(0, 4000, n // 8)
+        scan_both(g, o, p, t)
+        compare_state(g, o)
+        close_both(g, o)
+    g.destroy()
