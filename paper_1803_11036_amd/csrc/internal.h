@@ -43,6 +43,17 @@ struct SuperPointDev {
 struct LiveCfg {
     uint32_t c1, c2, wrap;
 };
+__host__ __device__ inline LiveCfg live_cfg(uint64_t t, uint32_t k, bool cell16)
+{
+    const uint32_t stamps = cell16 ? 65535u : 255u;
+    const uint32_t cur = 1u + (uint32_t)(t % stamps);
+    const bool wrap = cur < k;
+    const uint32_t lo = wrap ? cur + stamps + 1u - k : cur - k + 1u, kp = wrap ? k + 1u : k;
+    if (cell16) return {lo, kp, wrap ? 1u : 0u};
+    return {(256u - lo) * 0x00010001u, (256u - kp) * 0x00010001u, wrap ? 1u : 0u};
+}
+// Every estimator has its dead cells cleared once in this many slots.
+__host__ __device__ inline uint32_t expire_period(uint32_t k, bool cell16) { return (cell16 ? 65535u : 255u) - k; }
 
 // One detector ("link") as every close kernel sees it.  Device resident; the
 // per-slice fields are written by k_prepare from the device clock at the start
@@ -190,8 +201,17 @@ struct DetectArgs {
     const uint64_t* se_prefix;    // [n_links + 1] waves before each link (a wave covers >= 4 KiB of state)
     uint32_t n_links;
     uint64_t total;               // waves launched
-    uint32_t expire_only;         // link 0 only: visit the estimators of this slot's expiry phase
     uint32_t stream;              // 1: the states read are larger than the Infinity Cache holds
+};
+
+// a slot that only advances: estimators phase, phase + period, ... lose their dead cells
+struct ExpireArgs {
+    uint8_t* state;
+    Clock* clock;
+    uint64_t n_se;
+    uint32_t chunks;              // 16-byte chunks of an estimator
+    uint32_t period, phase;
+    LiveCfg L;
 };
 
 struct LevelArgs {
@@ -219,8 +239,8 @@ struct PackArgs {
 };
 
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
-hipError_t launch_prepare(const LinkDesc* links, uint32_t n_links, bool clear_hot, hipStream_t s);
-hipError_t launch_advance(const LinkDesc* links, uint32_t n_links, hipStream_t s);
+hipError_t launch_prepare(const LinkDesc* links, uint32_t n_links, hipStream_t s);
+hipError_t launch_expire(const ExpireArgs& a, bool cell16, hipStream_t s);
 hipError_t launch_gather_ctl(const LinkDesc* links, uint32_t n_links, Ctl* dst, hipStream_t s);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
 // one link's call, keeping its exact counters (the open slice's stamp, and slot mod k)
@@ -263,7 +283,7 @@ hipError_t launch_recount(const LinkDesc* link, uint64_t n_se, hipStream_t s);
 uint32_t count_workgroups(uint64_t n_se);
 hipError_t launch_count_multi(const CountMultiArgs& m, uint32_t total_wg, hipStream_t s);
 hipError_t launch_hot_detect(const DetectArgs& a, uint32_t max_chunks_per_lane, bool small, hipStream_t s);
-// hot detection (or, with expire_only, the rotating expiry) of one link of 16-bit cells
+// hot detection of one link of 16-bit cells
 hipError_t launch_hot_detect16(const DetectArgs& a, hipStream_t s);
 hipError_t launch_hot_compact(const LinkDesc* links, const uint32_t* row_table, uint32_t rows, hipStream_t s);
 hipError_t launch_expand0(const LevelArgs& a, hipStream_t s);

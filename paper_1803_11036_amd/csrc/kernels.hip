@@ -210,49 +210,54 @@ __global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v)
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// Per-slice constants of every link from its device clock (the open slice t).
 // Per-slice constants of every link from its slot clock (grid: links x 16,
 // thread 0 of block (l, 0)), and the hot bitmasks cleared for this close.
-__global__ __launch_bounds__(256) void k_prepare(LinkDesc* links, uint32_t clear_hot)
+__global__ __launch_bounds__(256) void k_prepare(LinkDesc* links)
 {
     const uint32_t l = blockIdx.x;
-    if (clear_hot) {
-        const LinkDesc* D = links + l;
-        uint32_t* p = reinterpret_cast<uint32_t*>(D->hotbits);     // hotT follows hotbits
-        const uint64_t n = D->hot_words;
-        for (uint64_t i = blockIdx.y * 256u + threadIdx.x; i < n; i += 256u * gridDim.y) p[i] = 0u;
-    }
+    const LinkDesc* D = links + l;
+    uint32_t* p = reinterpret_cast<uint32_t*>(D->hotbits);     // hotT follows hotbits
+    const uint64_t n = D->hot_words;
+    for (uint64_t i = blockIdx.y * 256u + threadIdx.x; i < n; i += 256u * gridDim.y) p[i] = 0u;
     if (blockIdx.y != 0 || threadIdx.x != 0) return;
     const unsigned long long t = links[l].clock->t;
     const uint32_t k = links[l].k;
-    if (links[l].cell16) {
-        // 16-bit cells: stamps 1 + t mod 65535, expiry period 65535 - k
-        const uint32_t cur = 1u + (uint32_t)(t % 65535u);
-        LiveCfg c;
-        if (cur >= k) { c.c1 = cur - k + 1u; c.c2 = k; c.wrap = 0u; }
-        else { c.c1 = cur + 65536u - k; c.c2 = k + 1u; c.wrap = 1u; }
-        links[l].L = c;
-        links[l].expire_period = 65535u - k;
-        links[l].expire_phase = (uint32_t)(t % (65535u - k));
-        return;
-    }
-    const uint32_t cur = 1u + (uint32_t)(t % 255u);
-    uint32_t lo, kp, wrap;
-    if (cur >= k) { lo = cur - k + 1u; kp = k; wrap = 0u; }
-    else { lo = cur + 256u - k; kp = k + 1u; wrap = 1u; }
-    LiveCfg c;
-    c.c1 = (256u - lo) * 0x00010001u;
-    c.c2 = (256u - kp) * 0x00010001u;
-    c.wrap = wrap;
-    links[l].L = c;
-    links[l].expire_period = 255u - k;
-    links[l].expire_phase = (uint32_t)(t % (255u - k));
+    const bool cell16 = links[l].cell16 != 0u;
+    links[l].L = live_cfg(t, k, cell16);
+    const uint32_t period = expire_period(k, cell16);
+    links[l].expire_period = period;
+    links[l].expire_phase = (uint32_t)(t % period);
 }
 
-__global__ void k_advance(const LinkDesc* links, uint32_t n_links)
+// A slot that only advances (one detector): the dead cells of this slot's
+// expiry phase cleared, a wave per estimator, and the clock moved.  The slot's
+// constants come with the launch, so that it is the only one (a launch for
+// them, one for the expiry and one for the clock were 8.8 us and three
+// launches for 320 MiB).
+template <bool C16>
+__global__ __launch_bounds__(256) void k_expire(ExpireArgs a)
 {
-    const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l < n_links) links[l].clock->t += 1ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.clock->t += 1ull;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t s = a.phase + ((uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6)) * a.period;
+    if (s >= a.n_se) return;
+    const uint32_t chunks = a.chunks;                // of 16 bytes, at least 64
+    uint4* se = reinterpret_cast<uint4*>(a.state) + s * chunks;
+    for (uint32_t c0 = lane; c0 < chunks; c0 += 256u) {
+        uint4 v[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) v[u] = se[c0 + 64u * u < chunks ? c0 + 64u * u : c0];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) {
+            if (c0 + 64u * u >= chunks) continue;
+            uint4 n;
+            n.x = C16 ? expire_word16(v[u].x, a.L) : expire_word(v[u].x, a.L);
+            n.y = C16 ? expire_word16(v[u].y, a.L) : expire_word(v[u].y, a.L);
+            n.z = C16 ? expire_word16(v[u].z, a.L) : expire_word(v[u].z, a.L);
+            n.w = C16 ? expire_word16(v[u].w, a.L) : expire_word(v[u].w, a.L);
+            if (n.x != v[u].x || n.y != v[u].y || n.z != v[u].z || n.w != v[u].w) se[c0 + 64u * u] = n;
+        }
+    }
 }
 
 // Copy every link's control block into one contiguous array (links whose
@@ -262,8 +267,6 @@ __global__ void k_gather_ctl(const LinkDesc* links, uint32_t n_links, Ctl* dst)
     const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l < n_links) dst[l] = *links[l].ctl;
 }
-
-// Clear every link's hot bitmasks (grid: links x 16 blocks).
 
 // ---------------------------------------------------------------- scan
 // Alg. 2 for every pair: one byte store per row.  `se_lo..se_hi` restricts
@@ -1129,29 +1132,20 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
     // batches of up to 256 links search the wave prefix in LDS (one coalesced
     // load per workgroup instead of a chain of dependent loads per wave)
     __shared__ unsigned long long pre_lds[SMALL ? 257 : 1];
-    const bool lds_prefix = SMALL && a.n_links > 1 && a.n_links <= 256u && !a.expire_only;
+    const bool lds_prefix = SMALL && a.n_links > 1 && a.n_links <= 256u;
     if (lds_prefix) {
         for (uint32_t i = threadIdx.x; i <= a.n_links; i += blockDim.x) pre_lds[i] = a.se_prefix[i];
         __syncthreads();
     }
     if (g >= a.total) return;
-    uint32_t l;
-    uint64_t s;                                         // first estimator of the wave
-    if (a.expire_only) {
-        l = 0;
-        s = a.links[0].expire_phase + g * a.links[0].expire_period;
-        if (s >= a.links[0].n_se) return;
-    } else {
-        const unsigned long long* pre = lds_prefix ? pre_lds : reinterpret_cast<const unsigned long long*>(a.se_prefix);
-        l = uniform(find_link(pre, a.n_links, g));
-        const uint32_t lg = a.links[l].log2eta;
-        s = (g - pre[l]) << (lg < 12u ? 12u - lg : 0u);
-    }
+    const unsigned long long* pre = lds_prefix ? pre_lds : reinterpret_cast<const unsigned long long*>(a.se_prefix);
+    const uint32_t l = uniform(find_link(pre, a.n_links, g));
+    const uint32_t lg = a.links[l].log2eta;
+    const uint64_t s = (g - pre[l]) << (lg < 12u ? 12u - lg : 0u);      // first estimator of the wave
     const LinkDesc* D = a.links + l;
     const uint32_t log2eta = D->log2eta;
     const LiveCfg L = D->L;
-    const bool count = !a.expire_only;
-    if (SMALL && log2eta < 12u && count) {
+    if (SMALL && log2eta < 12u) {
         // several estimators per wave: four rounds of 1 KiB, one estimator per
         // 2^(log2eta-10) rounds; every estimator is whole in this wave
         const uint32_t rpe = 1u << (log2eta - 10);       // rounds per estimator (1 or 2)
@@ -1196,13 +1190,11 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
             v[c] = g0 + c >= per_lane ? make_uint4(0u, 0u, 0u, 0u)
                    : STREAM           ? load_stream(se + (g0 + c) * 64u + lane)
                                       : se[(g0 + c) * 64u + lane];
-        if (count) {
 #pragma unroll
-            for (int c = 0; c < CH; c++)
-                if (g0 + c < per_lane)
-                    live += __popc(live_bits(v[c].x, L)) + __popc(live_bits(v[c].y, L)) +
-                            __popc(live_bits(v[c].z, L)) + __popc(live_bits(v[c].w, L));
-        }
+        for (int c = 0; c < CH; c++)
+            if (g0 + c < per_lane)
+                live += __popc(live_bits(v[c].x, L)) + __popc(live_bits(v[c].y, L)) +
+                        __popc(live_bits(v[c].z, L)) + __popc(live_bits(v[c].w, L));
         if (expire) {
 #pragma unroll
             for (int c = 0; c < CH; c++) {
@@ -1215,18 +1207,16 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
             }
         }
     }
-    if (count) {
-        live = wave_sum(live);
-        if (per_lane <= (uint32_t)CH && live >= D->T) {
-            // the whole estimator is still in registers: snapshot from there
-            uint16_t* snap = D->live16 + s * (per_lane * 64u);
+    live = wave_sum(live);
+    if (per_lane <= (uint32_t)CH && live >= D->T) {
+        // the whole estimator is still in registers: snapshot from there
+        uint16_t* snap = D->live16 + s * (per_lane * 64u);
 #pragma unroll
-            for (int c = 0; c < CH; c++)
-                if ((uint32_t)c < per_lane) snap[c * 64u + lane] = (uint16_t)live_mask16(v[c], L);
-            hot_finish<false>(D, s, live, se, lane);
-        } else {
-            hot_finish<true>(D, s, live, se, lane);
-        }
+        for (int c = 0; c < CH; c++)
+            if ((uint32_t)c < per_lane) snap[c * 64u + lane] = (uint16_t)live_mask16(v[c], L);
+        hot_finish<false>(D, s, live, se, lane);
+    } else {
+        hot_finish<true>(D, s, live, se, lane);
     }
 }
 
@@ -1234,8 +1224,7 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect(DetectArgs a)
 // in round c lane j takes the 16 cells of snapshot word c * 64 + j (two
 // 16-byte chunks, so a wave reads 2 KiB in one go).  Up to CH rounds stay in
 // registers for the snapshot of a hot estimator; larger estimators are read
-// again.  With expire_only, only the estimators of this slot's expiry phase
-// are visited (and not counted).
+// again.
 template <int CH, bool STREAM>
 __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect16(DetectArgs a)
 {
@@ -1243,17 +1232,12 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect16(DetectArgs a
     const uint64_t g = (uint64_t)blockIdx.x * DETECT_WAVES + (threadIdx.x >> 6);
     if (g >= a.total) return;
     const LinkDesc* D = a.links;
-    uint64_t s = g;
-    if (a.expire_only) {
-        s = D->expire_phase + g * D->expire_period;
-        if (s >= D->n_se) return;
-    }
+    const uint64_t s = g;
     const uint32_t log2eta = D->log2eta;
     const LiveCfg L = D->L;
     const uint32_t rounds = (1u << log2eta) >> 10;      // 1024 cells per wave round (eta >= 1024)
     uint4* se = reinterpret_cast<uint4*>(D->state + (s << (log2eta + 1)));
     const bool expire = (s % D->expire_period) == D->expire_phase;
-    const bool count = !a.expire_only;
     uint32_t live = 0;
     uint32_t snap[CH];
     for (uint32_t g0 = 0; g0 < rounds; g0 += CH) {
@@ -1285,7 +1269,6 @@ __global__ __launch_bounds__(64 * DETECT_WAVES) void k_hot_detect16(DetectArgs a
             }
         }
     }
-    if (!count) return;
     live = wave_sum(live);
     if (live >= D->T) {
         uint16_t* out = D->live16 + s * (1u << (log2eta - 4));
@@ -2517,15 +2500,18 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_prepare(const LinkDesc* links, uint32_t n_links, bool clear_hot, hipStream_t s)
+hipError_t launch_prepare(const LinkDesc* links, uint32_t n_links, hipStream_t s)
 {
-    k_prepare<<<dim3(n_links, clear_hot ? 16 : 1), 256, 0, s>>>(const_cast<LinkDesc*>(links), clear_hot ? 1u : 0u);
+    k_prepare<<<dim3(n_links, 16), 256, 0, s>>>(const_cast<LinkDesc*>(links));
     return hipGetLastError();
 }
 
-hipError_t launch_advance(const LinkDesc* links, uint32_t n_links, hipStream_t s)
+hipError_t launch_expire(const ExpireArgs& a, bool cell16, hipStream_t s)
 {
-    k_advance<<<grid_for(n_links, 256, 64), 256, 0, s>>>(links, n_links);
+    if (a.period == 0 || a.chunks < 64u) return hipErrorInvalidValue;
+    const uint32_t waves = (uint32_t)((a.n_se + a.period - 1) / a.period), grid = (waves + 3u) / 4u;
+    if (cell16) k_expire<true><<<grid, 256, 0, s>>>(a);
+    else k_expire<false><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 

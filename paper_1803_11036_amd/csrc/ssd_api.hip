@@ -908,7 +908,7 @@ int enqueue_close_head(Engine* e)
 {
     const hipStream_t s = e->stream;
     LinkDesc* links = e->dev_links();
-    HIPCHK(e, launch_prepare(links, e->n, true, s));
+    HIPCHK(e, launch_prepare(links, e->n, s));
     // per link: R_k from the per-slot counters (1), from counters rebuilt
     // from the state first (2), or by reading the whole state (0)
     const uint32_t n = e->n;
@@ -1155,8 +1155,8 @@ int collect_results(Engine* e, bool packed, uint64_t single_prefix)
     return SSD_OK;
 }
 
-// Rotating expiry only (a router that only advances): per-slice constants,
-// the estimators of this slot's expiry phase, clock advance.
+// Rotating expiry only (a router that only advances): the estimators of this
+// slot's expiry phase and the clock, in one launch.
 int enqueue_advance_only(Engine* e)
 {
     const hipStream_t s = e->stream;
@@ -1164,17 +1164,18 @@ int enqueue_advance_only(Engine* e)
     e->count_rebuild[0] = 0;
     e->count_small[0] = 0;
     e->direct[0] = 0;
-    LinkDesc* links = e->dev_links();
-    HIPCHK(e, launch_prepare(links, e->n, false, s));
-    DetectArgs da{};
-    da.links = links;
-    da.se_prefix = e->at<uint64_t>(e->L.se_prefix);
-    da.n_links = 1;
-    da.expire_only = 1;
-    const uint64_t period = (e->hl[0].cell16 ? 65535u : 255u) - e->p[0].k;
-    da.total = (e->hl[0].n_se + period - 1) / period;
-    HIPCHK(e, e->hl[0].cell16 ? launch_hot_detect16(da, s) : launch_hot_detect(da, e->max_chunks, e->detect_small, s));
-    HIPCHK(e, launch_advance(links, e->n, s));
+    const LinkDesc& D = e->hl[0];
+    const uint32_t k = e->p[0].k;
+    const bool c16 = D.cell16 != 0;
+    ExpireArgs x{};
+    x.state = D.state;
+    x.clock = D.clock;
+    x.n_se = D.n_se;
+    x.chunks = (uint32_t)((e->p[0].eta << (c16 ? 1 : 0)) / 16u);
+    x.period = expire_period(k, c16);
+    x.phase = (uint32_t)(e->clock % x.period);
+    x.L = live_cfg(e->clock, k, c16);
+    HIPCHK(e, launch_expire(x, c16, s));
     return SSD_OK;
 }
 
