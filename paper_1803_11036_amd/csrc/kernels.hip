@@ -2171,18 +2171,24 @@ __device__ __forceinline__ void ctl_to_host(const LinkDesc* D, unsigned long lon
 }
 
 // The list of up to sort_limit (<= SORT_SMALL) keys in two launches, ranked by
-// counting: every key's ip is compared with every other, 64 keys of a
-// workgroup in its lanes, the others split over its 16 waves and read from
-// LDS.  n^2 comparisons spread over the chip are far cheaper than one
-// workgroup's sort, a chain of log2(n)^2 / 2 barriers on one compute unit.
+// counting: every key's ip is compared with every other, RANK_KEYS keys of a
+// workgroup at a time, each by 32 lanes that share the others, read from LDS.
+// n^2 comparisons spread over the chip are far cheaper than one workgroup's
+// sort, a chain of log2(n)^2 / 2 barriers on one compute unit, or than a
+// launch per step of it and a host that waits for the list's length (7000
+// hosts: 49 us with 64 keys a workgroup, 16 lanes each, and one load in
+// flight, 28 so; 11300 hosts: a close of 667 us with the multi-kernel sort,
+// 350 so).
 //   k_sort_keep: a key stays if no other of its ip comes before it (larger R,
 //   or equal and earlier in the list); n_out counts them.  A kept key's ip
 //   goes to the link's idle candidate buffers (which hold at least as many
 //   tuples as passed; the flags to their he_0 half), the others become 2^32 -
 //   1 there, above or equal to every ip.
 //   k_sort_place: the place of a kept key is the number of kept ips below its.
-// Grid: links x workgroups, each taking 64 keys in turn.  Lists above the
-// link's limit are left to the multi-kernel sort.
+// Grid: links x workgroups, each taking RANK_KEYS keys in turn.  Lists above
+// the link's limit are left to the multi-kernel sort.
+constexpr uint32_t RANK_KEYS = 32;
+static_assert(SORT_SMALL % 128u == 0u, "ips are read in rounds of 128");
 
 // The number of keys of this link's list that the small sort takes (0: none).
 __device__ __forceinline__ uint32_t rank_keys(const LinkDesc* D)
@@ -2198,78 +2204,89 @@ __device__ __forceinline__ uint32_t* rank_ips(const LinkDesc* D)
 }
 __device__ __forceinline__ uint32_t* rank_flags(const LinkDesc* D) { return D->ctb_h0[((D->r - 3u) & 1u) ^ 1u]; }
 
-// This wave's share of n values, four at a time (a multiple of 4 padded with
-// 2^32 - 1 is in `ips`): f(value, index).
+// n values of a workgroup into LDS, padded with 2^32 - 1 to whole rounds of
+// 128; four loads of a thread in flight.
 template <class F>
-__device__ __forceinline__ void for_ips(const uint32_t* ips, uint32_t n, F f)
+__device__ __forceinline__ void load_ips(uint32_t* ips, uint32_t n, F value)
 {
-    const uint32_t quads = (n + 3u) >> 2, per = (quads + 15u) >> 4, wave = threadIdx.x >> 6;
-    const uint32_t q1 = min(quads, (wave + 1u) * per);
-    for (uint32_t j = wave * per; j < q1; j++) {
-        const uint4 v = reinterpret_cast<const uint4*>(ips)[j];
-        f(v.x, 4u * j);
-        f(v.y, 4u * j + 1u);
-        f(v.z, 4u * j + 2u);
-        f(v.w, 4u * j + 3u);
+    const uint32_t padded = (n + 127u) & ~127u;
+    for (uint32_t i0 = threadIdx.x; i0 < padded; i0 += 4096u) {
+        uint32_t v[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) v[u] = value(min(i0 + 1024u * u, n - 1u));
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) {
+            const uint32_t i = i0 + 1024u * u;
+            if (i < padded) ips[i] = i < n ? v[u] : ~0u;
+        }
     }
 }
 
 __global__ __launch_bounds__(1024) void k_sort_keep(const LinkDesc* links)
 {
     __shared__ __align__(16) uint32_t ips[SORT_SMALL];
-    __shared__ uint32_t before[64];
+    __shared__ uint32_t before[RANK_KEYS];
     const LinkDesc* D = links + blockIdx.x;
-    const uint32_t n = rank_keys(D), lane = threadIdx.x & 63u;
-    if (blockIdx.y * 64u >= n) return;
+    const uint32_t n = rank_keys(D), lane = threadIdx.x & (RANK_KEYS - 1u), share = threadIdx.x / RANK_KEYS;
+    if (blockIdx.y * RANK_KEYS >= n) return;
     const unsigned long long* keys = D->acc;
     uint32_t *kept = rank_ips(D), *flags = rank_flags(D);
-    for (uint32_t i = threadIdx.x; i < ((n + 3u) & ~3u); i += 1024u) ips[i] = i < n ? (uint32_t)(keys[i] >> 32) : ~0u;
-    for (uint32_t i0 = blockIdx.y * 64u; i0 < n; i0 += gridDim.y * 64u) {
+    load_ips(ips, n, [&](uint32_t i) { return (uint32_t)(keys[i] >> 32); });
+    const uint4* quads = reinterpret_cast<const uint4*>(ips);
+    uint32_t n_kept = 0;
+    for (uint32_t i0 = blockIdx.y * RANK_KEYS; i0 < n; i0 += gridDim.y * RANK_KEYS) {
         const uint32_t i = i0 + lane;
         const unsigned long long k = i < n ? keys[i] : 0ull;
         const uint32_t ip = (uint32_t)(k >> 32);
-        if (threadIdx.x < 64u) before[lane] = 0u;
+        if (threadIdx.x < RANK_KEYS) before[lane] = 0u;
         __syncthreads();
-        for_ips(ips, n, [&](uint32_t o, uint32_t j) {
-            if (o == ip && j != i && j < n) {          // rare: another tuple regained this ip
-                const unsigned long long ko = keys[j];
-                if (ko < k || (ko == k && j < i)) before[lane] = 1u;
+#pragma unroll 4
+        for (uint32_t j = share; 4u * j < n; j += 32u) {
+            const uint4 v = quads[j];
+            if (v.x != ip && v.y != ip && v.z != ip && v.w != ip) continue;
+            // the key itself or, rarely, another tuple that regained its ip
+            for (uint32_t o = 4u * j; o < min(n, 4u * j + 4u); o++) {
+                if (ips[o] != ip || o == i) continue;
+                const unsigned long long ko = keys[o];
+                if (ko < k || (ko == k && o < i)) before[lane] = 1u;
             }
-        });
+        }
         __syncthreads();
-        if (threadIdx.x < 64u) {
-            const bool stays = i < n && !before[lane];
-            if (i < n) {
-                kept[i] = stays ? ip : ~0u;
-                flags[i] = stays ? 1u : 0u;
-            }
-            const uint64_t m = __ballot(stays);
-            if (lane == 0) atomicAdd(&D->ctl->n_out, (unsigned long long)__popcll(m));
+        if (threadIdx.x < RANK_KEYS && i < n) {
+            const bool stays = !before[lane];
+            kept[i] = stays ? ip : ~0u;
+            flags[i] = stays ? 1u : 0u;
+            n_kept += (uint32_t)__popcll(__ballot(stays));
         }
         __syncthreads();
     }
+    if (threadIdx.x == 0) atomicAdd(&D->ctl->n_out, (unsigned long long)n_kept);
 }
 
 __global__ __launch_bounds__(1024) void k_sort_place(const LinkDesc* links)
 {
     __shared__ __align__(16) uint32_t ips[SORT_SMALL];
-    __shared__ uint32_t below[64];
+    __shared__ uint32_t below[RANK_KEYS];
     const LinkDesc* D = links + blockIdx.x;
-    const uint32_t n = rank_keys(D), lane = threadIdx.x & 63u;
+    const uint32_t n = rank_keys(D), lane = threadIdx.x & (RANK_KEYS - 1u), share = threadIdx.x / RANK_KEYS;
     const uint32_t *kept = rank_ips(D), *flags = rank_flags(D);
-    if (blockIdx.y * 64u < n)
-        for (uint32_t i = threadIdx.x; i < ((n + 3u) & ~3u); i += 1024u) ips[i] = i < n ? kept[i] : ~0u;
-    for (uint32_t i0 = blockIdx.y * 64u; i0 < n; i0 += gridDim.y * 64u) {
+    if (blockIdx.y * RANK_KEYS < n) load_ips(ips, n, [&](uint32_t i) { return kept[i]; });
+    const uint4* quads = reinterpret_cast<const uint4*>(ips);
+    for (uint32_t i0 = blockIdx.y * RANK_KEYS; i0 < n; i0 += gridDim.y * RANK_KEYS) {
         const uint32_t i = i0 + lane;
         const bool stays = i < n && flags[i];
-        if (threadIdx.x < 64u) below[lane] = 0u;
+        if (threadIdx.x < RANK_KEYS) below[lane] = 0u;
         __syncthreads();
         const uint32_t ip = i < n ? ips[i] : 0u;
         uint32_t c = 0;
-        for_ips(ips, n, [&](uint32_t o, uint32_t) { c += o < ip ? 1u : 0u; });
+#pragma unroll 4
+        for (uint32_t j = share; 4u * j < n; j += 32u) {
+            const uint4 v = quads[j];
+            c += (v.x < ip ? 1u : 0u) + (v.y < ip ? 1u : 0u) + (v.z < ip ? 1u : 0u) + (v.w < ip ? 1u : 0u);
+        }
         if (c) atomicAdd(&below[lane], c);
         __syncthreads();
-        if (threadIdx.x < 64u && stays) {
+        if (threadIdx.x < RANK_KEYS && stays) {
             const uint32_t at = below[lane], R = 0xFFFFFFFFu - (uint32_t)D->acc[i];
             SuperPointDev sp;
             sp.ip = ip; sp.rk = R; sp.est = estimate(D->eta, R);
@@ -2803,8 +2820,8 @@ hipError_t launch_verify(const LevelArgs& a, hipStream_t s)
 
 hipError_t launch_sort_small(const LinkDesc* links, uint32_t n_links, hipStream_t s)
 {
-    // a workgroup per 64 keys for one link; several links share the chip
-    const dim3 g(n_links, n_links == 1 ? SORT_SMALL / 64u : 16u);
+    // one link: a workgroup for every compute unit; several links share the chip
+    const dim3 g(n_links, n_links == 1 ? 256u : 16u);
     k_sort_keep<<<g, 1024, 0, s>>>(links);
     k_sort_place<<<g, 1024, 0, s>>>(links);
     return hipGetLastError();

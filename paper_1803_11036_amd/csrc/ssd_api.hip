@@ -1913,7 +1913,7 @@ int ssd_set_tuning(ssd_detector* d, uint32_t knob, uint64_t value)
         }
         return SSD_OK;
     case SSD_TUNE_SORT_BLOCK_LIMIT: {
-        if (value > SORT_SMALL) return fail(SSD_E_PARAM, "sort block limit above %u", SORT_SMALL);
+        if (value > SORT_TUNE_MAX) return fail(SSD_E_PARAM, "sort block limit above %u", SORT_TUNE_MAX);
         if (close_pending(d)) return fail(SSD_E_ORDER, "a close is pending (ssd_close_end first)");
         int rc = usable(&d->e);
         if (rc) return rc;

@@ -82,3 +82,20 @@ def test_list_sizes(hosts, limit):
     res = close_both(g, o)
     assert len(res) >= hosts * 0.9
     g.destroy()
+
+
+@pytest.mark.parametrize("q,r,delta,kb,theta,rehash,n", [
+    (7, 4, 4, 15, 18, True, 52500), (7, 4, 4, 15, 18, True, 53000), (7, 4, 4, 15, 18, True, 55500),
+    (7, 4, 4, 15, 18, True, 55700), (6, 5, 3, 14, 10, False, 24000)])
+def test_long_lists(q, r, delta, kb, theta, rehash, n):
+    """Crowded estimators that accept 8100, 9095, 15310 and 15640 hosts (lists ranked by counting hold 15360 keys), and
+    about 9000 keys of 7000 hosts that false tuples regain."""
+    log(f"long list q={q} n={n}")
+    g, o = make_pair(q, r, delta, 1024, 1, theta, tg.hash_tables(11), key_bits=kb, rehash=rehash, max_tuples=1 << 23)
+    rng = np.random.default_rng(n)
+    p = np.empty((n, 2), dtype=np.uint32)
+    p[:, 0] = rng.integers(0, 1 << kb, n)
+    p[:, 1] = rng.integers(0, 1 << 32, n, dtype=np.uint32)
+    scan_both(g, o, p, 0)
+    close_both(g, o)
+    g.destroy()
