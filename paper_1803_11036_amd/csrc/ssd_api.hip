@@ -452,6 +452,7 @@ struct Engine {
     bool direct_mailbox = false;       // the sort kernel writes control block and list to pinned memory
     // graph replay of the close
     bool use_graph = false;
+    bool graph_asked = false;         // the caller set it (else a short synchronous close is launched directly)
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipStream_t capture_stream = nullptr;   // records the close graph (never runs work)
@@ -1884,7 +1885,10 @@ int ssd_set_tuning(ssd_detector* d, uint32_t knob, uint64_t value)
     switch (knob) {
     case SSD_TUNE_SCAN_PASS_BYTES: d->pass_bytes = value; return SSD_OK;
     case SSD_TUNE_TIMING: d->e.timing = value != 0; return SSD_OK;
-    case SSD_TUNE_GRAPH: d->e.use_graph = value != 0; return SSD_OK;
+    case SSD_TUNE_GRAPH:
+        d->e.use_graph = value != 0;
+        d->e.graph_asked = true;
+        return SSD_OK;
     case SSD_TUNE_SCAN_MODE:
         if (value != SSD_SCAN_PASSES && value != SSD_SCAN_BINNED && value != SSD_SCAN_AUTO)
             return fail(SSD_E_PARAM, "unknown scan mode %llu", (unsigned long long)value);
@@ -2067,7 +2071,14 @@ int ssd_close_slice(ssd_detector* d, uint32_t flags, ssd_super_point* out_host, 
     HIPCHK(e, hipStreamWaitEvent(e->stream, d->close_done, 0));     // a pipelined close before it
     rc = enqueue_close_head(e);
     if (rc) return rc;
-    rc = e->use_graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
+    // The tail is five launches up to DFS_MAX_ROWS rows, and a caller who waits
+    // for the list has it sooner from them than from the graph, whose first
+    // kernel starts later than the fifth launch returns: 61 against 75 us for a
+    // slot of 4099 pairs into 24 MiB, 120 against 132 for one of a million.  More rows add
+    // a launch each, and a pipelined close, which nobody waits for, keeps the
+    // graph (415 us a slot against 428 on the core link).
+    const bool graph = e->use_graph && (e->graph_asked || e->max_r > DFS_MAX_ROWS);
+    rc = graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
     if (rc) return rc;
     HIPCHK(e, hipEventRecord(d->close_done, e->stream));
     d->pending = true;

@@ -99,3 +99,26 @@ def test_long_lists(q, r, delta, kb, theta, rehash, n):
     scan_both(g, o, p, 0)
     close_both(g, o)
     g.destroy()
+
+
+@pytest.mark.parametrize("q,r,delta", [(12, 6, 5), (8, 12, 2)])
+def test_closes_of_both_kinds(q, r, delta):
+    """Waited-for and pipelined closes in turn, launched directly or replayed as a graph by the number of rows, and
+    both as asked for: lists as the oracle's."""
+    kb = min(32, (r - 2) * delta + q)
+    g, o = make_pair(q, r, delta, 1024, 3, 24, tg.hash_tables(5), key_bits=kb, rehash=True, max_tuples=1 << 22)
+    for t in range(9):
+        log(f"close kinds r={r} slot {t}")
+        if t in (5, 7):
+            ssd.set_tuning(g, ssd.SSD_TUNE_GRAPH, t == 7)
+        scan_both(g, o, _pairs(t, 30, 40, kb, t), t)
+        if t % 3 == 1:
+            ssd.close_begin(g)
+            got = ssd.close_end(g)
+            o.reconstruct()
+            ip, rk, _ = o.results()
+            assert np.array_equal(got["ip"], ip) and np.array_equal(got["rk"], rk)
+            o.age()
+        else:
+            close_both(g, o)
+    g.destroy()
