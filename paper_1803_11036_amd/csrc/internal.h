@@ -44,12 +44,11 @@ struct SuperPointDev {
 struct LiveCfg {
     uint32_t c1, c2, wrap;
 };
-__host__ __device__ inline LiveCfg live_cfg(uint64_t t, uint32_t k, bool cell16)
+__host__ __device__ inline uint32_t slot_stamp(uint64_t t, bool cell16) { return 1u + (uint32_t)(t % (cell16 ? 65535u : 255u)); }
+__host__ __device__ inline LiveCfg live_cfg(uint32_t cur, uint32_t k, bool cell16)      // cur: the closed slot's stamp
 {
-    const uint32_t stamps = cell16 ? 65535u : 255u;
-    const uint32_t cur = 1u + (uint32_t)(t % stamps);
     const bool wrap = cur < k;
-    const uint32_t lo = wrap ? cur + stamps + 1u - k : cur - k + 1u, kp = wrap ? k + 1u : k;
+    const uint32_t lo = wrap ? cur + (cell16 ? 65536u : 256u) - k : cur - k + 1u, kp = wrap ? k + 1u : k;
     if (cell16) return {lo, kp, wrap ? 1u : 0u};
     return {(256u - lo) * 0x00010001u, (256u - kp) * 0x00010001u, wrap ? 1u : 0u};
 }
@@ -57,8 +56,9 @@ __host__ __device__ inline LiveCfg live_cfg(uint64_t t, uint32_t k, bool cell16)
 __host__ __device__ inline uint32_t expire_period(uint32_t k, bool cell16) { return (cell16 ? 65535u : 255u) - k; }
 
 // One detector ("link") as every close kernel sees it.  Device resident; the
-// per-slice fields are written by k_prepare from the device clock at the start
-// of every close, so a captured close replays with fixed arguments.
+// per-slice fields are written on the device (k_prepare from the clock before
+// a close; a single detector's close leaves the next slot's), so a captured
+// close replays with fixed arguments.
 struct Clock {
     unsigned long long t;         // open slice
 };
@@ -90,6 +90,7 @@ struct LinkDesc {
     // per slice
     LiveCfg L;
     uint32_t expire_period, expire_phase;
+    uint32_t cur;                 // the open slot's stamp
 };
 
 // direct scan of one detector, one pass window
@@ -292,7 +293,8 @@ hipError_t launch_expand0(const LevelArgs& a, hipStream_t s);
 hipError_t launch_expand_dfs(LevelArgs a, uint32_t max_r, uint32_t max_delta, uint64_t table_bytes, hipStream_t s);
 hipError_t launch_extend(const LevelArgs& a, hipStream_t s);
 hipError_t launch_verify(const LevelArgs& a, hipStream_t s);
-hipError_t launch_sort_small(const LinkDesc* links, uint32_t n_links, hipStream_t s);
+// (next: the last kernel also prepares the link's next slot, in k_prepare's place)
+hipError_t launch_sort_small(LinkDesc* links, uint32_t n_links, bool next, hipStream_t s);
 hipError_t launch_sort_large(const LinkDesc* link, const LinkDesc& host_copy, unsigned long long* tmp, uint64_t n,
                              hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);

@@ -449,6 +449,7 @@ struct Engine {
     double ph_ms[N_PHASES] = {};
     uint64_t ph_launches[N_PHASES] = {};
     bool gather_ctl = false;           // control blocks live with their links (groups)
+    bool prepared = false;             // the last close left the device's constants and hot bitmasks for this slot
     bool direct_mailbox = false;       // the sort kernel writes control block and list to pinned memory
     // graph replay of the close
     bool use_graph = false;
@@ -909,7 +910,8 @@ int enqueue_close_head(Engine* e)
 {
     const hipStream_t s = e->stream;
     LinkDesc* links = e->dev_links();
-    HIPCHK(e, launch_prepare(links, e->n, s));
+    if (!e->prepared) HIPCHK(e, launch_prepare(links, e->n, s));
+    e->prepared = false;              // (until this close's last kernel is enqueued)
     // per link: R_k from the per-slot counters (1), from counters rebuilt
     // from the state first (2), or by reading the whole state (0)
     const uint32_t n = e->n;
@@ -1028,7 +1030,7 @@ int enqueue_close_tail(Engine* e, bool pack, uint64_t single_prefix, bool captur
     HIPCHK(e, launch_verify(la, s));
     end(pm, 4, 1);
     pm = begin();
-    HIPCHK(e, launch_sort_small(links, e->n, s));
+    HIPCHK(e, launch_sort_small(links, e->n, e->direct_mailbox, s));
     end(pm, 5, 1);
     if (e->direct_mailbox) return SSD_OK;   // k_sort_place wrote the mailbox and advanced the clock
     if (e->gather_ctl) HIPCHK(e, launch_gather_ctl(links, e->n, e->at<Ctl>(e->L.ctl), s));
@@ -1162,6 +1164,7 @@ int enqueue_advance_only(Engine* e)
 {
     const hipStream_t s = e->stream;
     e->count_valid[0] = 0;            // the next slot's counters are not zeroed
+    e->prepared = false;
     e->count_rebuild[0] = 0;
     e->count_small[0] = 0;
     e->direct[0] = 0;
@@ -1175,7 +1178,7 @@ int enqueue_advance_only(Engine* e)
     x.chunks = (uint32_t)((e->p[0].eta << (c16 ? 1 : 0)) / 16u);
     x.period = expire_period(k, c16);
     x.phase = (uint32_t)(e->clock % x.period);
-    x.L = live_cfg(e->clock, k, c16);
+    x.L = live_cfg(slot_stamp(e->clock, c16), k, c16);
     HIPCHK(e, launch_expire(x, c16, s));
     return SSD_OK;
 }
@@ -2015,6 +2018,7 @@ int ssd_close_begin(ssd_detector* d)
     }
     e->stream = caller;
     if (rc) return rc;
+    e->prepared = true;
     d->pending = true;
     d->pending_prefix = prefix;
     e->clock++;
@@ -2081,6 +2085,7 @@ int ssd_close_slice(ssd_detector* d, uint32_t flags, ssd_super_point* out_host, 
     rc = graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
     if (rc) return rc;
     HIPCHK(e, hipEventRecord(d->close_done, e->stream));
+    e->prepared = true;
     d->pending = true;
     d->pending_prefix = prefix;
     e->clock++;
@@ -2244,6 +2249,7 @@ int ssd_import_state(ssd_detector* d, const void* blob_host, uint64_t n)
     HIPCHK(e, hipMemcpyAsync(d->D().clock, &c, sizeof c, hipMemcpyHostToDevice, e->stream));
     HIPCHK(e, hipStreamSynchronize(e->stream));
     e->clock = h.clock;
+    e->prepared = false;
     // the counters are not in the blob: stale, rebuilt from the state after
     // the next large binned call, else the next close reads the state
     e->count_valid[0] = 0;
@@ -2998,6 +3004,7 @@ int ssd_group_close_begin(ssd_group* g, ssd_detector* const* members, uint32_t n
         e->count_rebuild[i] = 0;
         me.count_valid[0] = e->count_valid[i];
         me.count_rebuild[0] = 0;
+        me.prepared = false;          // the group's close moves the clock and leaves the bitmasks
         me.count_small[0] = 0;
         me.direct[0] = 0;
     }

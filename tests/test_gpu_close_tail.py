@@ -9,7 +9,7 @@ import pytest
 
 import paper_1803_11036_amd as ssd
 import tracegen as tg
-from _parity import close_both, log, make_pair, scan_both
+from _parity import close_both, compare_state, log, make_pair, scan_both
 
 pytestmark = pytest.mark.gpu
 
@@ -121,4 +121,46 @@ def test_closes_of_both_kinds(q, r, delta):
             o.age()
         else:
             close_both(g, o)
+    g.destroy()
+
+
+@pytest.mark.parametrize("cell_bits,k", [(8, 3), (8, 20), (16, 5)])
+def test_slots_prepared_by_the_close_before(cell_bits, k):
+    """A close leaves the next slot's constants and cleared bitmasks: past the wraps of the stamps and of the expiry
+    phase, and after everything that moves the clock another way (advance-only slots, group closes, a resumed state)."""
+    def fresh():
+        return make_pair(8, 4, 4, 1024, k, 30, tg.hash_tables(2), key_bits=16, rehash=True, cell_bits=cell_bits,
+                         max_tuples=1 << 20)
+    g, o = fresh()
+    group = ssd.Group(4) if cell_bits == 8 else None
+    for t in range(530):
+        kind = "own" if t % 7 else ("advance", "group", "begin", "resume")[t // 7 % 4]
+        if kind == "group" and group is None:
+            kind = "own"
+        if kind == "resume":
+            blob = ssd.export_state(g)
+            g.destroy()
+            g = fresh()[0]
+            ssd.import_state(g, blob)
+        if t % 3 == 0 or t % 7 < 2:
+            scan_both(g, o, _pairs(t, 6, 60, 16, t), t)
+        o.reconstruct()
+        ip, rk, _ = o.results()
+        if kind == "advance":
+            ssd.close_slice(g, advance_only=True)
+        else:
+            if kind == "group":
+                lists, status = ssd.group_close(group, [g])
+                assert status[0] == 0
+                got = lists[0]
+            elif kind == "begin":
+                ssd.close_begin(g)
+                got = ssd.close_end(g)
+            else:
+                got = ssd.close_slice(g)
+            assert np.array_equal(got["ip"], ip) and np.array_equal(got["rk"], rk), f"slot {t} ({kind})"
+        o.age()
+        if t % 50 == 49:
+            log(f"prepared slots bits={cell_bits} k={k} slot {t}")
+            compare_state(g, o)
     g.destroy()
