@@ -221,7 +221,7 @@ BinPlan bin_plan(const ssd_params& p, uint64_t bin_bytes)
     while (((state + (1ull << b.shift) - 1) >> b.shift) > MAX_BINS) b.shift++;
     b.n_bins = (uint32_t)((state + (1ull << b.shift) - 1) >> b.shift);
     b.pb = (BIN_LDS_WORDS - 2048u - b.n_bins - 1u) / p.r;
-    // rows 5 and 6 keep every pair's offsets in registers (k_bin_reg): at
+    // rows 5 and 6 keep every pair's hashes and ranks in registers (bin_reg): at
     // most 7 and 6 pairs per thread
     if (p.r == 6) b.pb = std::min<uint32_t>(b.pb, 6u * 1024u);
     if (p.r == 5) b.pb = std::min<uint32_t>(b.pb, 7u * 1024u);
@@ -453,7 +453,7 @@ struct Engine {
     bool direct_mailbox = false;       // the sort kernel writes control block and list to pinned memory
     // graph replay of the close
     bool use_graph = false;
-    bool graph_asked = false;         // the caller set it (else a short synchronous close is launched directly)
+    bool graph_asked = false;         // the caller set it (else a single detector's short close is launched directly)
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipStream_t capture_stream = nullptr;   // records the close graph (never runs work)
@@ -1099,6 +1099,19 @@ int close_graph(Engine* e, bool pack, uint64_t prefix)
     int rc = enqueue_close_head(e);
     if (rc) return rc;
     return close_graph_tail(e, pack, prefix);
+}
+
+// The tail of a single detector's close.  It is five launches up to
+// DFS_MAX_ROWS rows, and a caller who waits for the list has it sooner from
+// them than from the graph, whose first kernel starts later than the fifth
+// launch returns: 61 against 75 us for a slot of 4099 pairs into 24 MiB, 120
+// against 132 for one of a million.  A pipelined close takes the same either
+// way (425.3 and 425.3 us a slot on the core link) and is spared the graph's
+// first instantiation (about 3 ms of a process).  More rows add a launch each.
+int detector_tail(Engine* e, uint64_t prefix)
+{
+    const bool graph = e->use_graph && (e->graph_asked || e->max_r > DFS_MAX_ROWS);
+    return graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
 }
 
 // After the close's synchronisation: check every link's capacities, finish
@@ -2011,7 +2024,7 @@ int ssd_close_begin(ssd_detector* d)
     HIPCHK(e, hipStreamWaitEvent(d->close_stream, d->detect_done, 0));
     const hipStream_t caller = e->stream;
     e->stream = d->close_stream;
-    rc = e->use_graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
+    rc = detector_tail(e, prefix);
     if (rc == SSD_OK) {
         hipError_t err = hipEventRecord(d->close_done, e->stream);
         if (err != hipSuccess) rc = dev_fail(e, err, "hipEventRecord");
@@ -2075,14 +2088,7 @@ int ssd_close_slice(ssd_detector* d, uint32_t flags, ssd_super_point* out_host, 
     HIPCHK(e, hipStreamWaitEvent(e->stream, d->close_done, 0));     // a pipelined close before it
     rc = enqueue_close_head(e);
     if (rc) return rc;
-    // The tail is five launches up to DFS_MAX_ROWS rows, and a caller who waits
-    // for the list has it sooner from them than from the graph, whose first
-    // kernel starts later than the fifth launch returns: 61 against 75 us for a
-    // slot of 4099 pairs into 24 MiB, 120 against 132 for one of a million.  More rows add
-    // a launch each, and a pipelined close, which nobody waits for, keeps the
-    // graph (415 us a slot against 428 on the core link).
-    const bool graph = e->use_graph && (e->graph_asked || e->max_r > DFS_MAX_ROWS);
-    rc = graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
+    rc = detector_tail(e, prefix);
     if (rc) return rc;
     HIPCHK(e, hipEventRecord(d->close_done, e->stream));
     e->prepared = true;

@@ -103,8 +103,8 @@ def test_long_lists(q, r, delta, kb, theta, rehash, n):
 
 @pytest.mark.parametrize("q,r,delta", [(12, 6, 5), (8, 12, 2)])
 def test_closes_of_both_kinds(q, r, delta):
-    """Waited-for and pipelined closes in turn, launched directly or replayed as a graph by the number of rows, and
-    both as asked for: lists as the oracle's."""
+    """Waited-for and pipelined closes in turn, launched directly or (more rows, or asked for) replayed as a graph:
+    lists as the oracle's."""
     kb = min(32, (r - 2) * delta + q)
     g, o = make_pair(q, r, delta, 1024, 3, 24, tg.hash_tables(5), key_bits=kb, rehash=True, max_tuples=1 << 22)
     for t in range(9):
