@@ -87,3 +87,23 @@ def test_runs_shared_by_lanes(cell_bits):
         compare_state(g, o)
         close_both(g, o)
     g.destroy()
+
+
+@pytest.mark.parametrize("n", [700_001, 1_000_003, 1_600_007])
+def test_calls_around_the_staging(n):
+    """Calls that half segments take in one step, in one more step than whole ones (which are then taken), and that
+    either take in several."""
+    g, o = make_pair(12, 6, 5, 1024, 2, 60, tg.hash_tables(7), rehash=True, max_tuples=1 << 22)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SCAN_MODE, ssd.SSD_SCAN_BINNED)
+    ssd.set_tuning(g, ssd.SSD_TUNE_SCAN_BIN_BYTES, 1 << 18)
+    rng = np.random.default_rng(n)
+    hosts = rng.integers(0, 1 << 32, 20_000, dtype=np.uint32)
+    for t in range(2):
+        p = np.empty((n, 2), dtype=np.uint32)
+        p[:, 0] = rng.choice(hosts, n)
+        p[:, 1] = rng.integers(0, 1 << 32, n, dtype=np.uint32)
+        scan_both(g, o, p, t)
+        compare_state(g, o)
+        ssd.close_slice(g, advance_only=True)
+        o.close(advance_only=True)
+    g.destroy()
