@@ -2697,7 +2697,9 @@ hipError_t launch_apply_counted(const ApplyArgs& a, hipStream_t s)
     if (!a.counts || a.k == 0 || a.slot >= a.k || a.bin_shift < a.log2eta || a.bin_shift < 5 ||
         bytes > COUNTED_LDS_BYTES || a.n_bins == 0)
         return hipErrorInvalidValue;
-    if (!a.pack || a.seg < 6u) return hipErrorInvalidValue;     // counted bins are at most 2 MiB: always packed
+    // counted bins are at most 2 MiB: always packed, and a segment of one offset
+    // or more is at least the pair of words that mark_runs reads at a time
+    if (!a.pack || a.seg == 0) return hipErrorInvalidValue;
     if (a.cell16) return hipErrorInvalidValue;                   // counters are kept for 8-bit cells only
     hipError_t e = counted_lds_attr();
     if (e != hipSuccess) return e;
