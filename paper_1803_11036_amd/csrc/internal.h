@@ -260,6 +260,8 @@ constexpr uint32_t BIN_CUS = 256u;
 // of its own gives every compute unit one workgroup.
 constexpr uint32_t BIN_MULTI_ROUNDS = 2u;
 constexpr uint32_t BIN_HALF_WORDS = 20480u - 32u;     // two workgroups a compute unit
+// Packed segments are written and read in 8- and 16-byte accesses.
+inline bool bin_items_aligned(const BinArgs& a) { return ((uintptr_t)a.items & 15u) == 0; }
 hipError_t launch_bin(const BinArgs& a, hipStream_t s);
 hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);
 hipError_t launch_apply_counted(const ApplyArgs& a, hipStream_t s);

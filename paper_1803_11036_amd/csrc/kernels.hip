@@ -2612,7 +2612,7 @@ uint32_t bin_workgroups(const BinArgs& a)      // segments dealt to XCDs in eigh
 hipError_t launch_bin(const BinArgs& a, hipStream_t s)
 {
     const uint32_t words = bin_lds_words(a.n_bins, a.pb, a.r);
-    if (a.blocks == 0 || a.rounds == 0 || words > BIN_LDS_WORDS) return hipErrorInvalidValue;
+    if (a.blocks == 0 || a.rounds == 0 || words > BIN_LDS_WORDS || !bin_items_aligned(a)) return hipErrorInvalidValue;
     hipError_t e = bin_lds_attr();
     if (e != hipSuccess) return e;
     const uint32_t grid = bin_workgroups(a), lds = words * 4u;

@@ -293,6 +293,11 @@ struct Layout {
     std::vector<LinkLayout> link;
 };
 
+// Words of a link's binning segments in a staging that several links share:
+// whole 128-byte lines, so that every link's segments start on one (they are
+// written and read in 8- and 16-byte accesses).
+uint64_t stage_words(uint64_t words) { return (words + 31u) & ~31ull; }
+
 // Arguments of a batch's multi-link binned launches for n links: per link
 // one BinArgs and one ApplyArgs, and the workgroup prefixes of the launches
 // (at most five per group of links -- two of binning, three of stores -- and at
@@ -379,7 +384,7 @@ Layout plan(const ssd_params* p, uint32_t n, uint64_t pack_cap, uint64_t tile_ca
             L.bin_table_words = std::max(L.bin_table_words, tw);
         }
         const uint64_t iw = std::min<uint64_t>(BATCH_BIN_PAIRS * rmax, cells / 4);
-        L.bin_items_words = std::max(L.bin_items_words, iw);
+        L.bin_items_words = stage_words(std::max(L.bin_items_words, iw));
         L.bin_table_words = std::max(L.bin_table_words, iw / 8 + MAX_BINS + 1);
         // the per-link arguments and workgroup prefixes of the multi-link launches
         L.multi_args = o;
@@ -1584,7 +1589,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
         Plan p{l, binned_call(e, l, np, DEFAULT_BIN_BYTES), 0, 0, 0};
         if (p.c.counted && (!p.c.csh || p.c.bp.shift != p.c.csh)) return fail(SSD_E_STATE, "counted bin plan mismatch");
         p.blocks = (np + p.c.bp.pb - 1) / p.c.bp.pb;
-        p.items = p.blocks * p.c.seg;
+        p.items = stage_words(p.blocks * p.c.seg);
         p.table = (uint64_t)(p.c.bp.n_bins + 1) * p.blocks;
         if (p.items > e->L.bin_items_words || p.table > e->L.bin_table_words || p.c.bp.shift > 21 || e->hl[l].cell16)
             alone.push_back(l);
@@ -1632,6 +1637,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
             BinArgs& x = ba[i - g0];
             ApplyArgs& y = aa[i - g0];
             binned_args(e, p.l, p.c, items + io, table + to, DEFAULT_APPLY_SEGMENTS, &x, &y);
+            if (!bin_items_aligned(x)) return fail(SSD_E_STATE, "misaligned binning segments of link %u", p.l);
             x.pairs = pairs + offsets[p.l];
             x.n = offsets[p.l + 1] - offsets[p.l];
             x.blocks = (uint32_t)p.blocks;
