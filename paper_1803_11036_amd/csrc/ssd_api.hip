@@ -366,7 +366,7 @@ Layout plan(const ssd_params* p, uint32_t n, uint64_t pack_cap, uint64_t tile_ca
     if (bins && n == 1) {
         uint64_t iw = 0, tw = 0;
         bin_capacity(p[0], &iw, &tw);
-        L.bin_items_words = iw;
+        L.bin_items_words = stage_words(iw);
         L.bin_table_words = tw;
     } else if (bins) {
         // a batch: the links binned in one group of launches share these
@@ -386,7 +386,10 @@ Layout plan(const ssd_params* p, uint32_t n, uint64_t pack_cap, uint64_t tile_ca
         const uint64_t iw = std::min<uint64_t>(BATCH_BIN_PAIRS * rmax, cells / 4);
         L.bin_items_words = stage_words(std::max(L.bin_items_words, iw));
         L.bin_table_words = std::max(L.bin_table_words, iw / 8 + MAX_BINS + 1);
-        // the per-link arguments and workgroup prefixes of the multi-link launches
+    }
+    if (bins && pack_cap) {
+        // a batch, of one link too: the per-link arguments and workgroup
+        // prefixes of the multi-link launches
         L.multi_args = o;
         o = align_up(o + multi_args_bytes(n));
     }
@@ -1598,6 +1601,7 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
     }
     // the arguments of every launch of this call, staged in pinned memory
     // and copied to the device once
+    if (!e->L.multi_args) return fail(SSD_E_STATE, "no room for the arguments of the binned launches");
     const uint64_t bin_region = 0;
     const uint64_t app_region = align_up((uint64_t)n * sizeof(BinArgs));
     const uint64_t pre_region = app_region + align_up((uint64_t)n * sizeof(ApplyArgs));

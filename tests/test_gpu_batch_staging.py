@@ -1,6 +1,6 @@
 """A batch's binned links side by side in one staging: binning segments whose
 offsets are no multiple of four (five rows), in odd numbers, so that every link but the first would start off the 16 bytes that
-segments are written and read in.  R_k and lists against the oracle."""
+segments are written and read in; and one link alone.  R_k and lists against the oracle."""
 import numpy as np
 import pytest
 
@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
     # q, r, delta, eta, pairs: 19, 22 and 21 segments of 3647 pairs of five rows
     [(14, 5, 6, 1024, 66_000), (14, 5, 6, 1024, 80_001), (14, 5, 6, 1024, 73_000), (12, 6, 5, 1024, 66_001)],
     # 19 segments of 3615, then links of six and nine rows
-    [(15, 5, 6, 1024, 65_536), (16, 6, 4, 1024, 70_001), (14, 9, 3, 1024, 70_001)]])
+    [(15, 5, 6, 1024, 65_536), (16, 6, 4, 1024, 70_001), (14, 9, 3, 1024, 70_001)],
+    # a batch of one link, which takes the same launches
+    [(12, 6, 5, 1024, 66_001)]])
 def test_links_side_by_side(spec):
     theta, k = 100, 2
     tabs = [tg.hash_tables(40 + i) for i in range(len(spec))]
