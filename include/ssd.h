@@ -252,8 +252,8 @@ int ssd_get_info(ssd_detector *d, ssd_info *out);
  *       over the whole state; default 128 MiB).  Passes sized to the device's
  *       last-level cache keep a pass's random byte stores cache-resident.
  *   SSD_TUNE_SORT_BLOCK_LIMIT: result lists up to this many accepted hosts
- *       are ranked by counting (at most 8192; 15360 unless set); longer
- *       lists use the multi-kernel sort. */
+ *       are ranked by counting, longer ones take the multi-kernel sort: 0 to
+ *       8191, or 8192, the largest value, for the default of 15360. */
 #define SSD_TUNE_SCAN_PASS_BYTES 1u
 #define SSD_TUNE_SORT_BLOCK_LIMIT 2u
 #define SSD_TUNE_TIMING 3u          /* 1: time every phase with HIP events */

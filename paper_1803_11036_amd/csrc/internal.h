@@ -9,7 +9,7 @@ namespace ssd {
 constexpr uint32_t MAX_ROWS = 16;
 constexpr uint32_t MAX_MERGE_SOURCES = 64;
 constexpr uint32_t SORT_SMALL = 15360;  // result lists up to this size are ranked by counting (k_sort_keep: 60 KiB of LDS)
-constexpr uint32_t SORT_TUNE_MAX = 8192;   // the largest limit that a caller may set
+constexpr uint32_t SORT_TUNE_MAX = 8192;   // the largest limit that a caller may set: it stands for SORT_SMALL, the default
 constexpr uint32_t MAX_LINKS = 1024;    // detectors in one batch
 constexpr uint32_t LEVEL_VERIFY = 0xFFFFu;
 constexpr uint32_t LEVEL_DFS = 0xFFFEu;

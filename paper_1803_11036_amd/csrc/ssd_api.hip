@@ -1966,7 +1966,7 @@ int ssd_set_tuning(ssd_detector* d, uint32_t knob, uint64_t value)
         if (close_pending(d)) return fail(SSD_E_ORDER, "a close is pending (ssd_close_end first)");
         int rc = usable(&d->e);
         if (rc) return rc;
-        d->e.hl[0].sort_limit = value;
+        d->e.hl[0].sort_limit = value == SORT_TUNE_MAX ? SORT_SMALL : value;     // the largest value: as never set
         HIPCHK(&d->e, hipMemcpyAsync(&d->e.dev_links()[0].sort_limit, &d->e.hl[0].sort_limit, 8,
                                      hipMemcpyHostToDevice, d->e.stream));
         HIPCHK(&d->e, hipStreamSynchronize(d->e.stream));
