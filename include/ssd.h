@@ -258,8 +258,7 @@ int ssd_get_info(ssd_detector *d, ssd_info *out);
 #define SSD_TUNE_SORT_BLOCK_LIMIT 2u
 #define SSD_TUNE_TIMING 3u          /* 1: time every phase with HIP events */
 #define SSD_TUNE_SCAN_TILE_PAIRS 4u /* batches: pairs per scan work tile (default 4096) */
-#define SSD_TUNE_GRAPH 5u           /* 1 (default) = replay the close as a HIP graph (detectors, batches; unless
-                                       set, a detector's few kernels are launched directly) */
+#define SSD_TUNE_GRAPH 5u           /* 1 (default) = replay the close as a HIP graph (detectors, batches) */
 #define SSD_TUNE_AUTOTUNE 6u        /* batches: 1 = tune on the next scans (reads 1 until
                                        done, 9 to 11 scans): the tile scan's (pass window,
                                        tile) pair, each of 9 timed on one scan; and the bin

@@ -461,7 +461,6 @@ struct Engine {
     bool direct_mailbox = false;       // the sort kernel writes control block and list to pinned memory
     // graph replay of the close
     bool use_graph = false;
-    bool graph_asked = false;         // the caller set it (else a single detector's short close is launched directly)
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipStream_t capture_stream = nullptr;   // records the close graph (never runs work)
@@ -1091,6 +1090,13 @@ int enqueue_close(Engine* e, bool pack, uint64_t single_prefix)
 // of our own (the caller's may be the legacy default stream, which cannot be
 // captured) and replayed on the caller's stream after the eager first part.
 // Recaptured when the result prefix it copies changes.
+// (A detector's tail is five launches up to DFS_MAX_ROWS rows, and a
+// waited-for close has its list sooner from them than from a replay: a slot
+// of 4099 pairs into 24 MiB, closes back to back, 57 us against 66.  But the
+// wait for the device or the stream that follows, with every kernel done,
+// then takes 24 to 40 us more, against 1 to 5 after a replay: slots after a
+// synchronisation or 0.3 to 10 ms of idle, that wait included, 86 to 121 us
+// with launches and 74 to 96 with the replay.)
 int close_graph_tail(Engine* e, bool pack, uint64_t prefix)
 {
     int rc = SSD_OK;
@@ -1126,19 +1132,6 @@ int close_graph(Engine* e, bool pack, uint64_t prefix)
     int rc = enqueue_close_head(e);
     if (rc) return rc;
     return close_graph_tail(e, pack, prefix);
-}
-
-// The tail of a single detector's close.  It is five launches up to
-// DFS_MAX_ROWS rows, and a caller who waits for the list has it sooner from
-// them than from the graph, whose first kernel starts later than the fifth
-// launch returns: 61 against 75 us for a slot of 4099 pairs into 24 MiB, 120
-// against 132 for one of a million.  A pipelined close takes the same either
-// way (425.3 and 425.3 us a slot on the core link) and is spared the graph's
-// first instantiation (about 3 ms of a process).  More rows add a launch each.
-int detector_tail(Engine* e, uint64_t prefix)
-{
-    const bool graph = e->use_graph && (e->graph_asked || e->max_r > DFS_MAX_ROWS);
-    return graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
 }
 
 // After the close's synchronisation: check every link's capacities, finish
@@ -1930,10 +1923,7 @@ int ssd_set_tuning(ssd_detector* d, uint32_t knob, uint64_t value)
     switch (knob) {
     case SSD_TUNE_SCAN_PASS_BYTES: d->pass_bytes = value; return SSD_OK;
     case SSD_TUNE_TIMING: d->e.timing = value != 0; return SSD_OK;
-    case SSD_TUNE_GRAPH:
-        d->e.use_graph = value != 0;
-        d->e.graph_asked = true;
-        return SSD_OK;
+    case SSD_TUNE_GRAPH: d->e.use_graph = value != 0; return SSD_OK;
     case SSD_TUNE_SCAN_MODE:
         if (value != SSD_SCAN_PASSES && value != SSD_SCAN_BINNED && value != SSD_SCAN_AUTO)
             return fail(SSD_E_PARAM, "unknown scan mode %llu", (unsigned long long)value);
@@ -2053,7 +2043,7 @@ int ssd_close_begin(ssd_detector* d)
     HIPCHK(e, hipStreamWaitEvent(d->close_stream, d->detect_done, 0));
     const hipStream_t caller = e->stream;
     e->stream = d->close_stream;
-    rc = detector_tail(e, prefix);
+    rc = e->use_graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
     if (rc == SSD_OK) {
         hipError_t err = hipEventRecord(d->close_done, e->stream);
         if (err != hipSuccess) rc = dev_fail(e, err, "hipEventRecord");
@@ -2117,7 +2107,7 @@ int ssd_close_slice(ssd_detector* d, uint32_t flags, ssd_super_point* out_host, 
     HIPCHK(e, hipStreamWaitEvent(e->stream, d->close_done, 0));     // a pipelined close before it
     rc = enqueue_close_head(e);
     if (rc) return rc;
-    rc = detector_tail(e, prefix);
+    rc = e->use_graph ? close_graph_tail(e, false, prefix) : enqueue_close_tail(e, false, prefix, false);
     if (rc) return rc;
     HIPCHK(e, hipEventRecord(d->close_done, e->stream));
     e->prepared = true;
