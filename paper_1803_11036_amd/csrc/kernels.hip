@@ -1653,7 +1653,11 @@ __global__ __launch_bounds__(256) void k_extend(LevelArgs a)
 //     back while it has candidates left.  So no queue ever holds more than
 //     127, and the lanes are full until the end.
 // All lookups go to LDS: the hot bits of rows 2..r-1, 2^q per row in key order
-// (bit (key << delta) + j), and the hot columns of rows 0 and 1.  The walk
+// (bit (key << delta) + j), and the hot columns of rows 0 and 1.  (A workgroup
+// of several links' launch with few pairs of a link reads that link's hot bits
+// where they are: filling LDS with them is most of its time.  24 links of few
+// hot columns 19.3 us with every table filled, 12.0 so, 64 links of many 52
+// and 45.)  The walk
 // counts the tuples and keeps a wave's first DFS_OUT full ones in LDS; the
 // workgroup then reserves its slots with one atomic, and a wave with more
 // tuples walks again to write them (atomics of one address pass at about 12 ns
@@ -1663,13 +1667,15 @@ __global__ __launch_bounds__(256) void k_extend(LevelArgs a)
 
 // A wave's view of the link it expands.
 struct DfsLink {
-    const uint32_t* tab;              // packed hot bits of rows 2..
+    const uint32_t* tab;              // packed hot bits of rows 2.. (short runs: not filled)
+    const uint64_t* keys;             // the same in memory, a word a key
     uint4* queue;                     // [r - 2][DFS_QUEUE]: x, he_0, candidates left
     uint2* out;                       // [DFS_OUT]: the wave's first full tuples (x, he_0)
     uint64_t* out_x;
     uint32_t* out_h0;
     uint64_t max_tuples;
     uint32_t words, delta, sh, kmask, qmask, key_bits, r;
+    bool in_lds;
 };
 
 // Orders a wave's LDS accesses across its lanes.
@@ -1688,6 +1694,7 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 // The candidates of `row` under a key, as a word of up to 2^6 bits.
 __device__ __forceinline__ uint64_t dfs_candidates(const DfsLink& d, uint32_t row, uint32_t key)
 {
+    if (!d.in_lds) return d.keys[((uint64_t)row << d.sh) + key];
     const uint32_t bit = key << d.delta;
     const uint32_t* w = d.tab + (row - 2u) * d.words + (bit >> 5);
     if (d.delta == 6u) return (uint64_t)w[1] << 32 | w[0];
@@ -1797,7 +1804,10 @@ __device__ __forceinline__ void dfs_walk(const DfsLink& d, const uint32_t* l0, c
 
 // One link's items are dealt to all waves in turn; several links' in
 // contiguous runs per workgroup, so that it meets few links and loads few
-// tables.
+// tables: none for a run of at most DFS_LOOKUP_ITEMS items a wave (64 links:
+// 52 us with every table loaded, 46 at 1 and 2, 45 at 4 and at 16).  A link
+// alone always loads its own (11 us for a small site's, 12 looked up).
+constexpr uint32_t DFS_LOOKUP_ITEMS = 4;
 template <int LEVELS, uint32_t WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
 {
@@ -1833,6 +1843,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
         d.out_x = D->ctb_x[lf & 1u];
         d.out_h0 = D->ctb_h0[lf & 1u];
         d.tab = tab;
+        d.keys = D->hotT;
+        d.in_lds = one || run_end - item > (uint64_t)DFS_LOOKUP_ITEMS * WAVES;
         d.queue = queues + wid * a.queue_rows * DFS_QUEUE;
         d.out = outs + wid * DFS_OUT;
         const uint32_t *l0 = D->hot_list, *l1 = D->hot_list + (1ull << D->q);
@@ -1847,7 +1859,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
             l0 = lists;
             l1 = lists + DFS_LIST;
         }
-        load_hot_table(D, d.words, tab);
+        if (d.in_lds) load_hot_table(D, d.words, tab);
         __syncthreads();
         const uint64_t it = one ? (uint64_t)wid * gridDim.x + blockIdx.x : item - link0 + wid;
         const uint64_t step = one ? (uint64_t)gridDim.x * WAVES : WAVES, it_end = run_end - link0;
