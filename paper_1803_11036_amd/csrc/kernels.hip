@@ -321,17 +321,42 @@ __global__ __launch_bounds__(256) void k_scan(ScanArgs a)
                      se_lo, se_hi, (T)a.stamp);
 }
 
+// Adds v to counter i (v depends on i alone) for the lanes that `on` holds
+// for.  A heavy host's pairs move the same counters, and atomics of one
+// address pass one after another: one lane adds for all of a wave that move
+// the same counter, counter by counter, up to 12 of them and until two were
+// moved by a lane alone (light hosts, whose lanes then add for themselves).
+// 65535 pairs of one host into each of 8 links of 384 MiB, eta = 16384: 852 us
+// with an atomic a lane, 435 so; of ten hosts 646 and 478; of as many hosts as
+// pairs 413 and 423.
+constexpr uint32_t COUNT_GROUPS = 12, COUNT_ALONE = 2;
+__device__ __forceinline__ void add_counts(uint32_t* counts, uint32_t i, uint32_t v, bool on)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint64_t left = __ballot(on);
+    for (uint32_t g = 0, alone = 0; g < COUNT_GROUPS && alone < COUNT_ALONE && left; g++) {
+        const uint32_t first = (uint32_t)__ffsll((long long)left) - 1u;
+        const uint64_t same = __ballot(on && i == (uint32_t)__builtin_amdgcn_readlane((int)i, (int)first)) & left;
+        if (lane == first) atomicAdd(&counts[i], v * (uint32_t)__popcll(same));
+        left &= ~same;
+        if (!(same & (same - 1ull))) alone++;
+    }
+    if ((left >> lane) & 1ull) atomicAdd(&counts[i], v);
+}
+
 // The same keeping exact counters exact, for calls with so few offsets that a
 // workgroup per bin costs more than they do: every cell's stamp is exchanged
 // by a compare-and-swap of its 32-bit word, and the one thread that changes it
 // moves its estimator's counters in memory (which slot, see k_apply_counted).
 // Six rows in flight.  Bound by random device-wide atomics, three for a cell
-// not yet stamped in the slice, 19 to 27 G/s: 5.8 G offsets/s.
+// not yet stamped in the slice (the exchange, and a counter up and one down or
+// the total up; more exchanges where threads meet in a word), 19 to 27 G/s:
+// 5.8 G offsets/s.
 __device__ __forceinline__ void scan_pair_counted(const uint32_t* tab, uint2 pr, const LinkDesc* D, uint32_t stamp,
                                                   uint32_t slot)
 {
     const uint32_t q = D->q, delta = D->delta, log2eta = D->log2eta, r = D->r, k = D->k;
-    const uint32_t qmask = (1u << q) - 1u;
+    const uint32_t qmask = (1u << q) - 1u, n_se = (uint32_t)D->n_se;
     uint32_t* words = reinterpret_cast<uint32_t*>(D->state);
     const uint32_t d = tab_hash(tab + 1024, pr.y) & ((1u << log2eta) - 1u);   // H1(oip)
     const uint32_t h0 = tab_hash(tab, pr.x) & qmask;                          // RHFG[0](cip)
@@ -359,13 +384,13 @@ __device__ __forceinline__ void scan_pair_counted(const uint32_t* tab, uint2 pr,
 #pragma unroll
             for (uint32_t u = 0; u < 6; u++) {
                 if (!((left >> u) & 1u)) continue;
-                if (was[u] == w[u]) {                          // this thread's stamp
-                    const uint32_t b = (w[u] >> sh) & 0xFFu, age = (stamp + 255u - b) % 255u;
-                    atomicAdd(&D->counts[(uint64_t)slot * D->n_se + se[u]], 1u);
-                    if (b && age < k) atomicAdd(&D->counts[(uint64_t)(slot >= age ? slot - age : slot + k - age) * D->n_se + se[u]], ~0u);
-                    else atomicAdd(&D->counts[(uint64_t)k * D->n_se + se[u]], 1u);
-                    left &= ~(1u << u);
-                }
+                const bool mine = was[u] == w[u];              // this thread's stamp
+                const uint32_t b = (w[u] >> sh) & 0xFFu, age = (stamp + 255u - b) % 255u;
+                const bool live = b && age < k;
+                const uint32_t at = live ? (slot >= age ? slot - age : slot + k - age) : k;
+                add_counts(D->counts, slot * n_se + (uint32_t)se[u], 1u, mine);
+                add_counts(D->counts, at * n_se + (uint32_t)se[u], live ? ~0u : 1u, mine);
+                if (mine) left &= ~(1u << u);
                 w[u] = was[u];
             }
         }

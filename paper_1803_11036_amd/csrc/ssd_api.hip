@@ -764,7 +764,11 @@ BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_byt
 // slice's calls so taken, this one included, have at most one offset per
 // `bytes` of a state above `above`.  Dropping the counters costs the close a
 // read of the whole state (5 TB/s); the direct scan takes as long for an
-// offset (5.8 G/s) as that read for 850 bytes.
+// offset (5.8 G/s) as that read for 850 bytes.  Calls of a few heavy hosts are
+// the slowest, at full budgets (slot with every state read against direct, and
+// direct with as many hosts as pairs): a detector of 768 MiB, eta = 16384, one
+// host 307 -> 111 us, ten 229 -> 134 (214 -> 78); 8 links of 384 MiB, eta =
+// 16384, one host 665 -> 534, ten 683 -> 577 (789 -> 505).
 bool direct_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bytes, uint64_t above)
 {
     const uint64_t state = state_bytes_of(e->p[l]);
