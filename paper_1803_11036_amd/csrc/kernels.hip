@@ -18,6 +18,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <initializer_list>
 #include <utility>
 
 #include "internal.h"
@@ -2617,26 +2619,34 @@ hipError_t launch_scan_tiles(const TileScanArgs& a, uint32_t blocks, hipStream_t
     return hipGetLastError();
 }
 
-// the dynamic LDS of the binning kernels, set once per kernel
-static hipError_t bin_lds_attr()
+// Kernels of more dynamic LDS than the default (kernel, bytes) are set up once
+// on every device, whichever thread launches one of them first.
+static hipError_t set_lds(std::atomic<uint64_t>& done, std::initializer_list<std::pair<const void*, uint64_t>> kernels)
 {
-    static bool attr = false;
-    if (attr) return hipSuccess;
-    const std::pair<const void*, uint32_t> kernels[] = {
-        {reinterpret_cast<const void*>(&k_bin<0, 0, false>), BIN_LDS_WORDS},
-        {reinterpret_cast<const void*>(&k_bin<6, 6, false>), BIN_LDS_WORDS},
-        {reinterpret_cast<const void*>(&k_bin<5, 7, false>), BIN_LDS_WORDS},
-        {reinterpret_cast<const void*>(&k_bin_multi_rows<false>), BIN_LDS_WORDS},
-        {reinterpret_cast<const void*>(&k_bin<0, 0, true>), BIN_HALF_WORDS},
-        {reinterpret_cast<const void*>(&k_bin<6, 3, true>), BIN_HALF_WORDS},
-        {reinterpret_cast<const void*>(&k_bin<5, 4, true>), BIN_HALF_WORDS},
-        {reinterpret_cast<const void*>(&k_bin_multi_rows<true>), BIN_HALF_WORDS}};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
     for (const auto& k : kernels) {
-        hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(k.second * 4u));
+        e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
         if (e != hipSuccess) return e;
     }
-    attr = true;
+    done.fetch_or(bit, std::memory_order_release);
     return hipSuccess;
+}
+
+static hipError_t bin_lds_attr()
+{
+    static std::atomic<uint64_t> done{0};
+    return set_lds(done, {{reinterpret_cast<const void*>(&k_bin<0, 0, false>), BIN_LDS_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin<6, 6, false>), BIN_LDS_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin<5, 7, false>), BIN_LDS_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin_multi_rows<false>), BIN_LDS_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin<0, 0, true>), BIN_HALF_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin<6, 3, true>), BIN_HALF_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin<5, 4, true>), BIN_HALF_WORDS * 4u},
+                          {reinterpret_cast<const void*>(&k_bin_multi_rows<true>), BIN_HALF_WORDS * 4u}});
 }
 
 bool bin_half(const BinArgs& a) { return bin_lds_words(a.n_bins, a.pb, a.r) <= BIN_HALF_WORDS; }
@@ -2704,28 +2714,18 @@ hipError_t launch_apply_marked16(const ApplyArgs& a, hipStream_t s)
 {
     if (!a.cell16 || !a.pack || a.bin_shift < 10 || a.bin_shift > MARKED16_MAX_SHIFT) return hipErrorInvalidValue;
     const uint32_t lds = (1u << (a.bin_shift - 5u)) * 4u;      // the bitmap
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_apply_marked16),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)MARKED16_LDS_MAX);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
+    static std::atomic<uint64_t> done{0};
+    hipError_t e = set_lds(done, {{reinterpret_cast<const void*>(&k_apply_marked16), MARKED16_LDS_MAX}});
+    if (e != hipSuccess) return e;
     k_apply_marked16<<<apply_counted_workgroups(a), 64 * CAPPLY_WAVES, lds, s>>>(a);
     return hipGetLastError();
 }
 
 static hipError_t counted_lds_attr()
 {
-    static bool attr = false;
-    if (attr) return hipSuccess;
-    for (const void* f : {reinterpret_cast<const void*>(&k_apply_counted),
-                          reinterpret_cast<const void*>(&k_apply_counted_multi)}) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)COUNTED_LDS_BYTES);
-        if (e != hipSuccess) return e;
-    }
-    attr = true;
-    return hipSuccess;
+    static std::atomic<uint64_t> done{0};
+    return set_lds(done, {{reinterpret_cast<const void*>(&k_apply_counted), COUNTED_LDS_BYTES},
+                          {reinterpret_cast<const void*>(&k_apply_counted_multi), COUNTED_LDS_BYTES}});
 }
 
 hipError_t launch_apply_counted(const ApplyArgs& a, hipStream_t s)
@@ -2851,14 +2851,10 @@ hipError_t launch_expand_dfs(LevelArgs a, uint32_t max_r, uint32_t max_delta, ui
     }
     a.level = LEVEL_DFS;
     a.queue_rows = max_r - 2u;
-    static bool attr = false;
-    if (!attr) {
-        for (const void* f : {reinterpret_cast<const void*>(&k_expand_dfs<4, 8>), reinterpret_cast<const void*>(&k_expand_dfs<6, 4>)}) {
-            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DFS_LDS_BYTES);
-            if (e != hipSuccess) return e;
-        }
-        attr = true;
-    }
+    static std::atomic<uint64_t> done{0};
+    hipError_t e = set_lds(done, {{reinterpret_cast<const void*>(&k_expand_dfs<4, 8>), DFS_LDS_BYTES},
+                                  {reinterpret_cast<const void*>(&k_expand_dfs<6, 4>), DFS_LDS_BYTES}});
+    if (e != hipSuccess) return e;
     if (max_r <= 6) k_expand_dfs<4, 8><<<DFS_BLOCKS, 512, (uint32_t)lds, s>>>(a);
     else k_expand_dfs<6, 4><<<DFS_BLOCKS, 256, (uint32_t)lds, s>>>(a);
     return hipGetLastError();
