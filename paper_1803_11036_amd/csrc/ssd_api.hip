@@ -104,6 +104,9 @@ constexpr uint64_t DEFAULT_PASS_BYTES = 128ull << 20;
 // L2 holds, and hashes all pairs for it.  1M uniform pairs of six rows: 6 MiB
 // 73 -> 37 us, 24 MiB 75 -> 62 us; 2^16 pairs 7.3 -> 5.9 and 7.8 -> 7.2 us,
 // 2^14 the same.  (48 MiB in two such passes: 78 -> 74 us and 7.9 -> 11.9.)
+// Only where a pass covers the state: with windows that a caller made smaller
+// every XCD would hash all pairs once for each (24 MiB in 3 MiB windows: a
+// million pairs 85 us shared, 181 by eighths; 2^18 pairs 47 and 59).
 constexpr uint64_t EIGHTHS_UP_TO = 24ull << 20;
 constexpr uint64_t EIGHTHS_MIN_PAIRS = 1ull << 16;
 constexpr uint64_t DEFAULT_TILE_PAIRS = 4096;
@@ -1387,8 +1390,8 @@ int enqueue_pass_scan(ssd_detector* d, const uint2* pairs, uint64_t n)
     const uint64_t n_se = D.n_se;
     uint64_t per_pass = n_se;
     if (d->pass_bytes) per_pass = std::max<uint64_t>(1, d->pass_bytes / ((uint64_t)D.eta << D.cell16));
-    a.eighths = state_bytes_of(e->p[0]) <= EIGHTHS_UP_TO && n >= EIGHTHS_MIN_PAIRS ? 1u : 0u;
     const uint64_t n_pass = (n_se + per_pass - 1) / per_pass;
+    a.eighths = n_pass == 1 && state_bytes_of(e->p[0]) <= EIGHTHS_UP_TO && n >= EIGHTHS_MIN_PAIRS ? 1u : 0u;
     PhaseMark pm = phase_begin(e);
     uint32_t launches = 0;
     for (uint64_t j = n_pass; j-- > 0;) {
