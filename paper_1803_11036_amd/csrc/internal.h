@@ -103,7 +103,7 @@ struct ScanArgs {
     uint64_t se_lo, se_hi;        // estimator window of this pass
     uint32_t stamp;
     uint32_t cell16;              // 1: 16-bit cells
-    uint32_t eighths;             // 1: the workgroups of every XCD store into an eighth of the window
+    uint32_t eighths;             // 1: the workgroups of every XCD may store into an eighth of the window (by_eighths)
 };
 
 // persistent batched scan: one estimator window of one link and that link's

@@ -292,9 +292,30 @@ __device__ __forceinline__ void scan_pair(const uint32_t* tab, uint2 pr, T* stat
     }
 }
 
-// With a.eighths, workgroup g stores only into eighth g mod 8 of the pass's
-// window.  Workgroup g runs on XCD g mod 8, so every XCD stores into a range
-// that its own L2 holds, where a window that all eight share is stored into
+// Whether a call of r rows is scanned by eighths, from 64 of its hosts, one a
+// lane, the same for every workgroup: not where few hosts bring much of the
+// call (a quarter, half from eight rows on), whose stores fall into few lines
+// that a shared window also keeps in the L2s.  Up to eight hosts of three
+// lanes or more are looked for.  Six rows, a million pairs into 24 MiB, shared
+// and by eighths: of as many hosts 77 and 72 us, Pareto 73 and 45, a fifth of
+// one host 61 and 61, half 42 and 46, ten hosts 28 and 53, one 16 and 38.
+// Eight rows, half of one host, 16 MiB: 54 and 49.
+__device__ __forceinline__ bool by_eighths(uint32_t host, uint32_t r)
+{
+    uint64_t left = ~0ull;
+    uint32_t heavy = 0;
+    for (uint32_t g = 0; g < 8u && left; g++) {
+        const uint64_t same = __ballot(host == (uint32_t)__builtin_amdgcn_readlane((int)host, __ffsll((long long)left) - 1)) & left;
+        const uint32_t c = (uint32_t)__popcll(same);
+        if (c > 2u) heavy += c;
+        left &= ~same;
+    }
+    return heavy <= (r < 8u ? 16u : 32u);
+}
+
+// By eighths (a.eighths, and the call's hosts: by_eighths) workgroup g stores
+// only into eighth g mod 8 of the pass's window.  Workgroup g runs on XCD g mod
+// 8, so every XCD stores into a range that its own L2 holds, where a window that all eight share is stored into
 // the Infinity Cache at 83 G/s (each L2 writes back its own bytes of a line).
 // Every XCD reads and hashes all pairs for it, which now bounds it (eight LDS
 // table lookups a pair), but takes only the one or two rows of its eighth.
@@ -303,11 +324,12 @@ template <class T>
 __global__ __launch_bounds__(256) void k_scan(ScanArgs a)
 {
     __shared__ uint32_t tab[2048];
+    const uint32_t sample = a.eighths ? a.pairs[(threadIdx.x & 63u) * (a.n >> 6)].x : 0u;
     for (uint32_t i = threadIdx.x; i < 2048u; i += 256u) tab[i] = a.tables[i];
     __syncthreads();
     uint64_t se_lo = a.se_lo, se_hi = a.se_hi;
     uint32_t g = blockIdx.x, grid = gridDim.x;
-    if (a.eighths) {
+    if (a.eighths && by_eighths(sample, (uint32_t)(a.se_hi >> a.q))) {
         const uint64_t per = (a.se_hi - a.se_lo + 7u) >> 3;
         se_lo = min(a.se_hi, a.se_lo + (g & 7u) * per);
         se_hi = min(a.se_hi, se_lo + per);

@@ -101,14 +101,18 @@ constexpr uint32_t PREFIX_MAX = SORT_SMALL;       // result entries staged in pi
 // workload; one pass when the state is smaller).
 constexpr uint64_t DEFAULT_PASS_BYTES = 128ull << 20;
 // States up to 8 x 3 MiB: every XCD stores into its own eighth, which its 4 MiB
-// L2 holds, and hashes all pairs for it.  1M uniform pairs of six rows: 6 MiB
-// 73 -> 37 us, 24 MiB 75 -> 62 us; 2^16 pairs 7.3 -> 5.9 and 7.8 -> 7.2 us,
-// 2^14 the same.  (48 MiB in two such passes: 78 -> 74 us and 7.9 -> 11.9.)
-// Only where a pass covers the state: with windows that a caller made smaller
-// every XCD would hash all pairs once for each (24 MiB in 3 MiB windows: a
-// million pairs 85 us shared, 181 by eighths; 2^18 pairs 47 and 59).
+// L2 holds, and hashes all pairs for it (38 us a million pairs at least).  1M
+// uniform pairs of six rows: 6 MiB 74 -> 38 us, 24 MiB 77 -> 72, Pareto hosts
+// 68 -> 40 and 73 -> 45.  (48 MiB in two such passes: 78 -> 74 us.)
+// - From 2^19 pairs: 530K Pareto pairs 34 -> 28 us, 270K 18 and 18, 140K 10 and
+//   12 (the kernel looks at 64 hosts first, about 1.5 us).
+// - From five rows: of three rows, uniform, 40 -> 45 us shared and by eighths.
+// - Where one pass covers the state: with windows that a caller made smaller
+//   every XCD would hash all pairs once for each (24 MiB in 3 MiB windows: a
+//   million pairs 85 us shared, 181 by eighths).
 constexpr uint64_t EIGHTHS_UP_TO = 24ull << 20;
-constexpr uint64_t EIGHTHS_MIN_PAIRS = 1ull << 16;
+constexpr uint64_t EIGHTHS_MIN_PAIRS = 1ull << 19;
+constexpr uint32_t EIGHTHS_MIN_ROWS = 5;
 constexpr uint64_t DEFAULT_TILE_PAIRS = 4096;
 constexpr uint64_t MAX_WINDOWS = 65536;           // batched scan windows per call
 constexpr uint64_t BATCH_STAGE = 16384;           // result entries staged by the batch graph
@@ -1391,7 +1395,8 @@ int enqueue_pass_scan(ssd_detector* d, const uint2* pairs, uint64_t n)
     uint64_t per_pass = n_se;
     if (d->pass_bytes) per_pass = std::max<uint64_t>(1, d->pass_bytes / ((uint64_t)D.eta << D.cell16));
     const uint64_t n_pass = (n_se + per_pass - 1) / per_pass;
-    a.eighths = n_pass == 1 && state_bytes_of(e->p[0]) <= EIGHTHS_UP_TO && n >= EIGHTHS_MIN_PAIRS ? 1u : 0u;
+    a.eighths = n_pass == 1 && D.r >= EIGHTHS_MIN_ROWS && state_bytes_of(e->p[0]) <= EIGHTHS_UP_TO &&
+                n >= EIGHTHS_MIN_PAIRS;
     PhaseMark pm = phase_begin(e);
     uint32_t launches = 0;
     for (uint64_t j = n_pass; j-- > 0;) {
