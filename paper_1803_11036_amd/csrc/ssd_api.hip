@@ -733,6 +733,7 @@ struct BinnedCall {
     bool large = false, counted = false, exact = false, marked = false;
     uint32_t csh = 0;        // counted bin shift (0: the link cannot count)
     BinPlan bp;
+    uint32_t whole_pb = 0;   // pairs of a whole segment (bp.pb: of the plan's)
     uint64_t seg = 0;        // offsets per binning workgroup (pb * r)
 };
 // Binning workgroups take half a compute unit (bin_half) where a bin's run in
@@ -755,6 +756,7 @@ BinnedCall binned_call(const Engine* e, uint32_t l, uint64_t n, uint64_t bin_byt
         c.marked = mp.shift <= MARKED16_MAX_SHIFT && n * e->p[l].r >= e->counted_min_items * mp.n_bins;
     }
     c.bp = bin_plan(e->p[l], c.counted ? 1ull << c.csh : c.marked ? MARKED16_BIN_BYTES : bin_bytes);
+    c.whole_pb = c.bp.pb;
     const uint32_t r = e->p[l].r, fixed = 2048u + c.bp.n_bins + 1u;
     if (halves && fixed < BIN_HALF_WORDS) {
         uint32_t pb = (BIN_HALF_WORDS - fixed) / r;
@@ -861,10 +863,9 @@ void binned_count_state(Engine* e, uint32_t l, const BinnedCall& c)
 }
 
 // The arguments of both binned steps of link l for its plan c, staging at
-// items / table, segments per store workgroup segs; pairs and sizes are set
-// per step.
-void binned_args(const Engine* e, uint32_t l, const BinnedCall& c, uint32_t* items, uint32_t* table, uint32_t segs,
-                 BinArgs* ba_out, ApplyArgs* aa_out)
+// items / table; pairs and sizes are set per step.
+void binned_args(const Engine* e, uint32_t l, const BinnedCall& c, uint32_t* items, uint32_t* table, BinArgs* ba_out,
+                 ApplyArgs* aa_out)
 {
     const LinkDesc& D = e->hl[l];
     const BinPlan bp = c.bp;
@@ -883,7 +884,6 @@ void binned_args(const Engine* e, uint32_t l, const BinnedCall& c, uint32_t* ite
     aa.n_bins = bp.n_bins;
     aa.seg = (uint32_t)c.seg;
     aa.bin_shift = bp.shift;
-    aa.per_part = segs;
     aa.stamp = stamp_of(e->clock, D.cell16);
     aa.cell16 = D.cell16;
     if (c.counted) {
@@ -895,6 +895,23 @@ void binned_args(const Engine* e, uint32_t l, const BinnedCall& c, uint32_t* ite
     }
     *ba_out = ba;
     *aa_out = aa;
+}
+
+// The segments of a step of m pairs in `blocks` segments, `segs` to a store
+// workgroup (uncounted stores, a wave each), or as many more as leave no more
+// workgroups than whole segments would take, where those of smaller ones are
+// more than STORE_WORKGROUPS: few offsets a wave cost more than the waves gain.
+// Two million pairs of ten hosts into 1.5 GiB: 75 us with whole segments, 114
+// with halves two to a workgroup, 74 so; of Pareto hosts 74, 117 and 80; 200K
+// Pareto pairs 31, 22 and 22.
+constexpr uint64_t STORE_WORKGROUPS = 1ull << 16;
+void store_split(const BinnedCall& c, uint64_t m, uint32_t blocks, uint32_t segs, ApplyArgs* aa)
+{
+    const uint64_t whole = (m + c.whole_pb - 1) / c.whole_pb, bins = c.bp.n_bins;
+    const uint64_t most = std::max({(whole + segs - 1) / segs, STORE_WORKGROUPS / bins, (uint64_t)1});
+    aa->blocks = blocks;
+    aa->per_part = (uint32_t)std::max<uint64_t>(segs, (blocks + most - 1) / most);
+    aa->parts = (blocks + aa->per_part - 1) / aa->per_part;
 }
 
 // Binned scan (k_bin, then k_apply_counted or k_apply) of n pairs of link l,
@@ -915,15 +932,14 @@ int enqueue_binned_scan(Engine* e, uint32_t l, const uint2* pairs, uint64_t n, u
     if (chunk == 0) return fail(SSD_E_STATE, "binned scan buffers too small");
     BinArgs ba{};
     ApplyArgs aa{};
-    binned_args(e, l, c, bb.items, bb.table, segs, &ba, &aa);
+    binned_args(e, l, c, bb.items, bb.table, &ba, &aa);
     for (uint64_t done = 0; done < n; done += chunk) {
         const uint64_t m = std::min(chunk, n - done);
         ba.pairs = pairs + done;
         ba.n = m;
         ba.blocks = (uint32_t)((m + bp.pb - 1) / bp.pb);
         ba.rounds = bin_half(ba) ? 1u : (ba.blocks + BIN_CUS - 1u) / BIN_CUS;
-        aa.blocks = ba.blocks;
-        aa.parts = (ba.blocks + aa.per_part - 1) / aa.per_part;
+        store_split(c, m, ba.blocks, segs, &aa);
         PhaseMark pm = phase_begin(e);
         HIPCHK(e, launch_bin(ba, e->stream));
         phase_end(e, pm, PHASE_SCAN_BIN, 1);
@@ -1645,14 +1661,13 @@ int enqueue_batch_binned(ssd_batch* b, const uint2* pairs, const uint64_t* offse
             binned_count_state(e, p.l, p.c);
             BinArgs& x = ba[i - g0];
             ApplyArgs& y = aa[i - g0];
-            binned_args(e, p.l, p.c, items + io, table + to, DEFAULT_APPLY_SEGMENTS, &x, &y);
+            binned_args(e, p.l, p.c, items + io, table + to, &x, &y);
             if (!bin_items_aligned(x)) return fail(SSD_E_STATE, "misaligned binning segments of link %u", p.l);
             x.pairs = pairs + offsets[p.l];
             x.n = offsets[p.l + 1] - offsets[p.l];
             x.blocks = (uint32_t)p.blocks;
             x.rounds = bin_half(x) ? 1u : BIN_MULTI_ROUNDS;
-            y.blocks = x.blocks;
-            y.parts = (y.blocks + y.per_part - 1) / y.per_part;
+            store_split(p.c, x.n, x.blocks, DEFAULT_APPLY_SEGMENTS, &y);
             io += p.items;
             to += p.table;
         }
@@ -2968,13 +2983,12 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
             const uint64_t np = std::min(b.chunk, b.n - b.done);
             BinArgs& ba = args[x].first;
             ApplyArgs& aa = args[x].second;
-            binned_args(&b.m->e, 0, b.c, b.bb.items, b.bb.table, b.m->apply_segments, &ba, &aa);
+            binned_args(&b.m->e, 0, b.c, b.bb.items, b.bb.table, &ba, &aa);
             ba.pairs = reinterpret_cast<const uint2*>(pairs_dev) + b.begin + b.done;
             ba.n = np;
             ba.blocks = (uint32_t)((np + b.c.bp.pb - 1) / b.c.bp.pb);
             ba.rounds = bin_half(ba) ? 1u : BIN_MULTI_ROUNDS;
-            aa.blocks = ba.blocks;
-            aa.parts = (aa.blocks + aa.per_part - 1) / aa.per_part;
+            store_split(b.c, np, ba.blocks, b.m->apply_segments, &aa);
             b.done += np;
         }
         for (uint32_t kind : {1u, 2u, 10u, 12u, 11u}) {
