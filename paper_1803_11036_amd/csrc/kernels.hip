@@ -1702,11 +1702,10 @@ __global__ __launch_bounds__(256) void k_extend(LevelArgs a)
 //     back while it has candidates left.  So no queue ever holds more than
 //     127, and the lanes are full until the end.
 // All lookups go to LDS: the hot bits of rows 2..r-1, 2^q per row in key order
-// (bit (key << delta) + j), and the hot columns of rows 0 and 1.  (A workgroup
-// of several links' launch with few pairs of a link reads that link's hot bits
-// where they are: filling LDS with them is most of its time.  24 links of few
-// hot columns 19.3 us with every table filled, 12.0 so, 64 links of many 52
-// and 45.)  The walk
+// (bit (key << delta) + j), and the hot columns of rows 0 and 1.  (Workgroups
+// with few pairs of a link read its hot bits where they are: filling LDS with
+// them is most of their time.  24 links of few hot columns 19.3 us with every
+// table filled, 12.0 so, 64 links of many 52 and 45.)  The walk
 // counts the tuples and keeps a wave's first DFS_OUT full ones in LDS; the
 // workgroup then reserves its slots with one atomic, and a wave with more
 // tuples walks again to write them (atomics of one address pass at about 12 ns
@@ -1855,8 +1854,11 @@ __device__ __forceinline__ void dfs_walk(const DfsLink& d, const uint32_t* l0, c
 // contiguous runs per workgroup, so that it meets few links and loads few
 // tables: none for a run of at most DFS_LOOKUP_ITEMS items a wave (64 links:
 // 52 us with every table loaded, 46 at 1 and 2, 45 at 4 and at 16).  A link
-// alone always loads its own (11 us for a small site's, 12 looked up).
-constexpr uint32_t DFS_LOOKUP_ITEMS = 4;
+// alone loads its table for more items a wave than the table has times
+// DFS_LOOKUP_WORDS words (of six rows of 2^16 columns 16: 3 hot columns a row
+// 16.2 us with the table and 9.1 looked up, 1300 28.6 and 19; of 2^12 columns
+// 1: 30 hot columns 12.2 and 12.5).
+constexpr uint32_t DFS_LOOKUP_ITEMS = 4, DFS_LOOKUP_WORDS = 512;
 template <int LEVELS, uint32_t WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
 {
@@ -1893,7 +1895,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
         d.out_h0 = D->ctb_h0[lf & 1u];
         d.tab = tab;
         d.keys = D->hotT;
-        d.in_lds = one || run_end - item > (uint64_t)DFS_LOOKUP_ITEMS * WAVES;
+        d.in_lds = one ? n_items > (uint64_t)gridDim.x * WAVES * ((d.r - 2u) * d.words / DFS_LOOKUP_WORDS)
+                       : run_end - item > (uint64_t)DFS_LOOKUP_ITEMS * WAVES;
         d.queue = queues + wid * a.queue_rows * DFS_QUEUE;
         d.out = outs + wid * DFS_OUT;
         const uint32_t *l0 = D->hot_list, *l1 = D->hot_list + (1ull << D->q);
@@ -1923,7 +1926,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_expand_dfs(LevelArgs a)
                         d.out_h0[slot + i] = v.y;
                     }
                 }
-            } else {
+            } else if (!pass || slot < d.max_tuples) {
                 dfs_walk(d, l0, l1, n0, n1, link_items, it, step, it_end, lv_wave[wid], pass != 0u, slot);
             }
             __syncthreads();
@@ -2011,10 +2014,10 @@ __device__ __forceinline__ void dfs_row(const LinkDesc* D, uint32_t he0, uint64_
 // A workgroup's slots for its threads' tuples of one link: the totals per
 // level to level_n, and this thread's first full-tuple slot (base of the
 // workgroup, then the tuples of the lanes and waves before it).  lv: tuples
-// per level (the last one are the full ones).  All threads call it.
+// per level (the last one are the full ones, *n_full).  All threads call it.
 template <int RMAX>
 __device__ __forceinline__ uint64_t reserve_tuples(const LinkDesc* D, const uint32_t* lv, uint32_t (*wsum)[RMAX],
-                                                   unsigned long long* base_slot)
+                                                   unsigned long long* base_slot, uint32_t* n_full)
 {
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     const uint32_t r = D->r, lf = r - 3;
@@ -2042,6 +2045,7 @@ __device__ __forceinline__ uint64_t reserve_tuples(const LinkDesc* D, const uint
     __syncthreads();
     uint64_t before = 0;
     for (uint32_t w = 0; w < wid; w++) before += wsum[w][lf];
+    *n_full = full;
     return *base_slot + before + (incl - full);
 }
 
@@ -2068,8 +2072,12 @@ __global__ __launch_bounds__(256) void k_expand_nested(LevelArgs a)
             uint64_t x;
             if (level0_pair(D, ch * 256u - pre[l] + threadIdx.x, &he0, &x)) dfs_row<2, RMAX, false>(D, he0, x, c);
         }
-        c.slot = reserve_tuples<RMAX>(D, c.lv, wsum, &base_slot);
-        for (uint64_t cw = chunk; cw < link_end; cw += gridDim.x) {
+        uint32_t full;
+        c.slot = reserve_tuples<RMAX>(D, c.lv, wsum, &base_slot, &full);
+        // (most threads have none to write: 2000 hosts into 2^17 columns 342 us with
+        // the second walk by all, 252 so; nor is there room past the buffer)
+        const bool writes = full && c.slot < D->max_tuples;
+        for (uint64_t cw = chunk; writes && cw < link_end; cw += gridDim.x) {
             uint32_t he0;
             uint64_t x;
             if (level0_pair(D, cw * 256u - pre[l] + threadIdx.x, &he0, &x)) dfs_row<2, RMAX, true>(D, he0, x, c);
