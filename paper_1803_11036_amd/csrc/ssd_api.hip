@@ -441,6 +441,7 @@ struct Engine {
     uint64_t counted_bin_bytes = DEFAULT_COUNTED_BIN_BYTES;   // bin size request of counted scans
     uint64_t counted_min_items = DEFAULT_COUNTED_MIN_ITEMS;   // offsets per bin a call needs to count through the bitmap
     std::vector<uint64_t> direct;          // per link: offsets of this slice's calls that kept the counters directly
+    uint64_t cells_written = 0;            // a detector's cells named by this slice's calls, its own and merges
     std::vector<uint8_t> count_small;      // a call of this slice stored uncounted for being small
     std::vector<uint8_t> last_mode;        // hot detection of the last close: 0 state, 1 counters, 2 rebuilt
     std::vector<uint64_t> bin_req;         // per link: bin size request of its counted scans (0: counted_bin_bytes)
@@ -952,6 +953,21 @@ int enqueue_binned_scan(Engine* e, uint32_t l, const uint2* pairs, uint64_t n, u
     return SSD_OK;
 }
 
+// Whether hot detection that reads `read` bytes of states loads past the
+// caches: states larger than the Infinity Cache, or twice that where links
+// share it (12 of 24 MiB: 111 us, 115 streamed; 24: 242 and 228) or cells have
+// 16 bits (320 MiB: 57 us, 63 streamed), that the slice's calls wrote a good
+// part of.  A quiet slice leaves little to write back, and streaming gains
+// nothing: 50K, 300K and a million pairs of five rows into 640 MiB of 16-bit
+// cells 121, 143 and 158 us, 141, 131 and 127 streamed; of six rows into 1.5
+// GiB 290, 322 and 366 us, 299, 285 and 303.
+bool streams(const Engine* e, uint64_t read)
+{
+    const bool c16 = e->hl[0].cell16 != 0;
+    if (read <= (c16 || e->n > 1 ? 2u : 1u) * AUTO_BINNED_ABOVE) return false;
+    return e->n > 1 || e->cells_written >= read / (c16 ? 1024u : 4096u);
+}
+
 // The close of every link: per-slice constants, hot bitmasks cleared, hot
 // detection (this first part, eager and timed), then hot lists, the
 // candidate levels, the final test, sorting, the control blocks (and, for
@@ -984,10 +1000,9 @@ int enqueue_close_head(Engine* e)
         da.se_prefix = e->at<uint64_t>(e->L.se_prefix);
         da.n_links = n;
         da.total = pre[n];
-        // (16-bit cells of 320 MiB, mostly in the Infinity Cache still: 57 us, 63 streamed)
         uint64_t read = 0;
         for (uint32_t l = 0; l < n; l++) read += mode[l] ? 0 : state_bytes_of(e->p[l]);
-        da.stream = read > (e->hl[0].cell16 ? 2u : 1u) * AUTO_BINNED_ABOVE ? 1u : 0u;
+        da.stream = streams(e, read);
         PhaseMark pm = phase_begin(e);
         // 16-bit cells only in single detectors (batches and groups take 8-bit links)
         HIPCHK(e, e->hl[0].cell16 ? launch_hot_detect16(da, s) : launch_hot_detect(da, e->max_chunks, e->detect_small, s));
@@ -1039,6 +1054,7 @@ int enqueue_close_head(Engine* e)
         e->count_small[l] = 0;
         e->direct[l] = 0;
     }
+    e->cells_written = 0;
     return SSD_OK;
 }
 
@@ -1228,6 +1244,7 @@ int enqueue_advance_only(Engine* e)
     e->count_rebuild[0] = 0;
     e->count_small[0] = 0;
     e->direct[0] = 0;
+    e->cells_written = 0;
     const LinkDesc& D = e->hl[0];
     const uint32_t k = e->p[0].k;
     const bool c16 = D.cell16 != 0;
@@ -1363,6 +1380,7 @@ int scan_checks(ssd_detector* d, const uint32_t* pairs_dev, uint64_t n, uint64_t
                     (unsigned long long)e->clock);
     if (n == 0) return SSD_OK;
     if (!pairs_dev || ((uintptr_t)pairs_dev & 7u)) return fail(SSD_E_PARAM, "pairs must be a non-NULL 8-byte aligned device pointer");
+    e->cells_written += n * e->p[0].r;
     return SSD_OK;
 }
 
@@ -2182,6 +2200,7 @@ int ssd_merge_router_state(ssd_detector* g, ssd_detector* const* routers, uint32
     }
     g->e.count_valid[0] = 0;          // merged cells are not counted
     g->e.count_rebuild[0] = 0;
+    g->e.cells_written += state_cells(gp);
     MergeArgs a{};
     a.dst = g->D().state;
     a.n16 = g->e.L.state_total / 16u;
@@ -2859,8 +2878,9 @@ int ssd_group_scan(ssd_group* g, ssd_detector* const* members, uint32_t n, const
     // the group's stream, so that the group's close stays ordered after them
     std::vector<uint8_t> in_bins(n, 0);
     for (uint32_t i = 0; i < n; i++) {
-        const ssd_detector* m = members[i];
+        ssd_detector* m = members[i];
         const uint64_t np = offsets_host[i + 1] - offsets_host[i];
+        m->e.cells_written += np * m->e.p[0].r;
         if (m->e.stream != e->stream || m->scan_mode == SSD_SCAN_PASSES) continue;
         in_bins[i] = np >= GROUP_BINNED_MIN_PAIRS && !direct_tiles(&m->e, 0, np, GROUP_BINNED_MIN_PAIRS);
     }
@@ -3058,6 +3078,7 @@ int ssd_group_close_begin(ssd_group* g, ssd_detector* const* members, uint32_t n
         me.prepared = false;          // the group's close moves the clock and leaves the bitmasks
         me.count_small[0] = 0;
         me.direct[0] = 0;
+        me.cells_written = 0;
     }
     rc = enqueue_close(e, true, 0);
     if (rc) return rc;
