@@ -307,8 +307,9 @@ int ssd_get_info(ssd_detector *d, ssd_info *out);
  *       the counters are exact and the state is large (above 256 MiB; links
  *       of batches and members of groups: 64 MiB), a small call keeps them
  *       exact pair by pair as long as the slice's small calls bring at most
- *       one cell offset per 4096 bytes of state (batches and groups: 1024,
- *       and at least 2^15 offsets); otherwise it stores uncounted.  An
+ *       one cell offset per 4096 bytes of state (batches and groups: per 1024
+ *       bytes, in calls of at least 2^15 offsets); otherwise it stores
+ *       uncounted.  An
  *       uncounted call, a router merge into the detector, an advance-only
  *       close or a pass scan leaves the counters stale: the close reads the
  *       state, or, when every binned call of the slice was large, rebuilds

@@ -1132,9 +1132,6 @@ __global__ __launch_bounds__(64 * CAPPLY_WAVES) void k_apply_marked16(ApplyArgs 
 
 constexpr uint32_t DETECT_WAVES = 4;   // waves (estimators) per workgroup (4, 8, 16 measured: 4 best)
 
-// The end of one estimator's test: R_k, and if hot, its live-cell snapshot
-// (for the final test, which then reads no state) and its bits in the row
-// and key-transposed bitmasks.
 // R_k of estimator s and, if it is hot, its bits in the row and
 // key-transposed bitmasks (lane 0 writes).
 __device__ __forceinline__ void hot_mark(const LinkDesc* D, uint64_t s, uint32_t live, uint32_t lane)
@@ -1156,6 +1153,8 @@ __device__ __forceinline__ void hot_mark(const LinkDesc* D, uint64_t s, uint32_t
     }
 }
 
+// The end of one estimator's test: hot_mark, and (SNAP) if hot its live-cell
+// snapshot for the final test, which then reads no state.
 template <bool SNAP>
 __device__ __forceinline__ void hot_finish(const LinkDesc* D, uint64_t s, uint32_t live, const uint4* se, uint32_t lane)
 {
@@ -2336,8 +2335,8 @@ __global__ __launch_bounds__(1024) void k_sort_keep(const LinkDesc* links)
 
 // next: the hot bitmasks, read for the last time by the expansion, are cleared
 // and the next slot's constants formed from this one's, so that its close
-// starts with the detection (with a launch of k_prepare before it a slot of a
-// million pairs took 123.4 us, now 121.6; 432 and 429 on the core link).
+// starts with the detection (a launch of k_prepare before it cost a slot 2 to 3
+// us).
 __global__ __launch_bounds__(1024) void k_sort_place(LinkDesc* links, uint32_t next)
 {
     __shared__ __align__(16) uint32_t ips[SORT_SMALL];
@@ -2870,7 +2869,7 @@ static uint64_t dfs_lds_bytes(uint32_t n_links, uint32_t rows, uint32_t waves, u
 hipError_t launch_expand_dfs(LevelArgs a, uint32_t max_r, uint32_t max_delta, uint64_t table_bytes, hipStream_t s)
 {
     if (max_r < 3 || max_r > 8) return hipErrorInvalidValue;
-    // eight waves' queues at r <= 6, four at r <= 8 (48 KiB both at the most rows)
+    // eight waves' queues at r <= 6 (64 KiB at six rows), four at r <= 8 (48 KiB at eight)
     const uint32_t waves = max_r <= 6 ? 8u : 4u;
     const uint64_t lds = dfs_lds_bytes(a.n_links, max_r - 2u, waves, table_bytes);
     if (lds > DFS_LDS_BYTES || max_delta > 6) {

@@ -1,8 +1,8 @@
 """The close's candidate expansion, final test and list ranking at the sizes
 where their kernels change path: rows and deltas of the queue walk and of the
 nested walk, waves with more full tuples than they stage, hot lists longer
-than the LDS copy, estimators of one to many loads per lane, lists around a
-workgroup's 64 keys and with hosts regained several times.  Every product
+than the LDS copy, estimators of one to many loads per lane, lists around a limit
+set to 64 and with hosts regained several times.  Every product
 against the oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -74,7 +74,7 @@ def test_final_test_against_oracle(log2eta, r, delta, q):
 @pytest.mark.parametrize("hosts", [0, 1, 63, 64, 65, 128, 1000])
 @pytest.mark.parametrize("limit", [8192, 64])
 def test_list_sizes(hosts, limit):
-    """Lists around a workgroup's 64 keys, also around the limit above which the multi-kernel sort takes them."""
+    """Short and long lists, also around a limit above which the multi-kernel sort takes them."""
     log(f"list of {hosts} hosts, limit {limit}")
     g, o = make_pair(16, 6, 4, 1024, 1, 16, tg.hash_tables(11), rehash=True)
     ssd.set_tuning(g, ssd.SSD_TUNE_SORT_BLOCK_LIMIT, limit)
@@ -103,8 +103,8 @@ def test_long_lists(q, r, delta, kb, theta, rehash, n):
 
 @pytest.mark.parametrize("q,r,delta", [(12, 6, 5), (8, 12, 2)])
 def test_closes_of_both_kinds(q, r, delta):
-    """Waited-for and pipelined closes in turn, launched directly or (more rows, or asked for) replayed as a graph:
-    lists as the oracle's."""
+    """Waited-for and pipelined closes in turn, replayed as a graph or (knob off) launched directly: lists as the
+    oracle's."""
     kb = min(32, (r - 2) * delta + q)
     g, o = make_pair(q, r, delta, 1024, 3, 24, tg.hash_tables(5), key_bits=kb, rehash=True, max_tuples=1 << 22)
     for t in range(9):
